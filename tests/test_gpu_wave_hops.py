@@ -1,0 +1,47 @@
+"""Subdomain hops with Ls a multiple of 4: the kernel that gives a wavefront 16
+output sites, at every Ls it takes, on tilings whose regions end inside a
+block of 16 sites and whose rim sites have one to eight of the eight terms.
+
+FP32 against the exact local operator within 1e-6, the bound of an FP32
+operator application; FP16 and INT8 against 2.5 times the error the format
+itself causes on this input (the oracle's model of the stored fields) plus
+1e-3 for the epilogue's FP16 operands, each within 2^-12 of its site column's
+largest value.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def rel(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+@pytest.mark.parametrize("Ls", [4, 8, 12, 16])
+@pytest.mark.parametrize("dims,sub", [((6, 6, 10, 6), (2, 6, 10, 2)), ((8, 6, 6, 4), (4, 2, 6, 4))])
+@pytest.mark.parametrize("prec", ["fp32", "fp16", "int8"])
+def test_local_operator_at_block_edges(dims, sub, Ls, prec):
+    from paper_2104_05615_amd import MSPCG
+    U = W.gauge_field(dims, 0.5, 31)
+    op = oracle.MobiusDWF(U, Ls, 1.5, 0.5, 1.8, 0.1)
+    til = oracle.Tiling(dims, sub)
+    g = np.random.default_rng(32).standard_normal((Ls, op.vh, 4, 3, 2))
+    r = g[..., 0] + 1j * g[..., 1]
+    vs = til.restrict(r)
+    exact = oracle.local_operator(op, til, vs)
+    tol = 1e-6
+    if prec != "fp32":
+        held = oracle.MobiusDWF(oracle.stored_links(U, prec), Ls, 1.5, 0.5, 1.8, 0.1)
+        tol = 2.5 * rel(oracle.local_operator_stored(held, til, vs, prec), exact) + 1e-3
+    s = MSPCG(dims)
+    s.load_gauge(U)
+    s.set_mobius(Ls, 1.5, 0.5, 1.8, 0.1)
+    s.set_subdomains(sub)
+    got = s.apply("A_sub", prec, r)
+    e = rel(got, til.prolong(exact, op.vh))
+    print(f"[gpu] A_sub {prec} dims={dims} sub={sub} Ls={Ls}: {e:.2e}, bound {tol:.2e}", flush=True)
+    assert e < tol
