@@ -106,6 +106,9 @@ void xpay_apply5(hipStream_t st, Prec p, const FieldPtr& out, const FieldPtr& pv
 // canon + r * nsites * Ls * 24)
 void pack_field(hipStream_t st, const FieldPtr& out, const double* canon, int64_t nsites, int Ls,
                 const Batch& bt = Batch());
+// out = the canonical field, out2 = E out
+void pack_apply5(hipStream_t st, const FieldPtr& out, const FieldPtr& out2, const void* E, const double* canon,
+                 int64_t nsites, int Ls);
 void unpack_field(hipStream_t st, double* canon, const FieldPtr& in, int64_t nsites, int Ls,
                   const Batch& bt = Batch());
 // p[0..n) = v (a kernel, so that graph capture records no memset)

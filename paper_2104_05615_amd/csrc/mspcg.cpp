@@ -737,18 +737,25 @@ struct mspcg_ctx {
     A_from_t0(st, p, out, in, t0, tag, norm_partial, bt);
   }
 
-  void D_op(hipStream_t st, Prec p, const FieldPtr& out, const FieldPtr& in, const std::string& tag) {
-    FieldPtr t0 = field(tag + ".t0", p, lat.vh), a = field(tag + ".a", p, lat.vh);
-    apply5_full(st, p, t0, in, mat(p, MAT_MPHI), lat.vh, Ls, nullptr);
+  // D and D^dag on `in`, given t0 = M_phi in (D) or M5^-dag in (D^dag)
+  void D_from_t0(hipStream_t st, Prec p, const FieldPtr& out, const FieldPtr& in, const FieldPtr& t0,
+            const std::string& tag) {
+    FieldPtr a = field(tag + ".a", p, lat.vh);
     hop(st, p, a, t0, nullptr, 1, false, epi(p, -1, MAT_Q));
     hop(st, p, out, a, &in, 0, false, epi(p, -1, MAT_NEG_M5INV, true));
   }
 
-  void Ddag_op(hipStream_t st, Prec p, const FieldPtr& out, const FieldPtr& in, const std::string& tag) {
-    FieldPtr t0 = field(tag + ".t0", p, lat.vh), e = field(tag + ".e", p, lat.vh);
-    apply5_full(st, p, t0, in, mat(p, MAT_M5INV_T), lat.vh, Ls, nullptr);
+  void Ddag_from_t0(hipStream_t st, Prec p, const FieldPtr& out, const FieldPtr& in, const FieldPtr& t0,
+                    const std::string& tag) {
+    FieldPtr e = field(tag + ".e", p, lat.vh);
     hop(st, p, e, t0, nullptr, 1, true, epi(p, -1, MAT_QT));
     hop(st, p, out, e, &in, 0, true, epi(p, -1, MAT_NEG_MPHI_T, true));
+  }
+
+  void Ddag_op(hipStream_t st, Prec p, const FieldPtr& out, const FieldPtr& in, const std::string& tag) {
+    FieldPtr t0 = field(tag + ".t0", p, lat.vh);
+    apply5_full(st, p, t0, in, mat(p, MAT_M5INV_T), lat.vh, Ls, nullptr);
+    Ddag_from_t0(st, p, out, in, t0, tag);
   }
 
   // A_s p_s for every subdomain (inner storage I), given t0 = M_phi p_s on C.
@@ -1974,6 +1981,16 @@ void apply_impl(mspcg_ctx* h, int op, Prec P, const double* in_dev, double* out_
     return;
   }
   FieldPtr fi = h->field("ap.in", P, vh), fo = h->field("ap.out", P, vh);
+  if (op == MSPCG_OP_D || op == MSPCG_OP_DDAG || op == MSPCG_OP_A) {
+    // the first fifth-dimension operator is applied with the conversion
+    FieldPtr t0 = h->field("ap.t0", P, vh);
+    pack_apply5(st, fi, t0, h->mat(P, op == MSPCG_OP_DDAG ? MAT_M5INV_T : MAT_MPHI), in_dev, vh, Ls);
+    if (op == MSPCG_OP_D) h->D_from_t0(st, P, fo, fi, t0, "ap");
+    else if (op == MSPCG_OP_DDAG) h->Ddag_from_t0(st, P, fo, fi, t0, "ap");
+    else h->A_from_t0(st, P, fo, fi, t0, "ap", nullptr);
+    unpack_field(st, out_dev, fo, vh, Ls);
+    return;
+  }
   pack_field(st, fi, in_dev, vh, Ls);
   switch (op) {
     case MSPCG_OP_DSLASH_EO: h->hop(st, P, fo, fi, nullptr, 0, false, Epilogue()); break;
@@ -1983,9 +2000,6 @@ void apply_impl(mspcg_ctx* h, int op, Prec P, const double* in_dev, double* out_
     case MSPCG_OP_M5: apply5_full(st, P, fo, fi, h->mat(P, MAT_M5), vh, Ls, nullptr); break;
     case MSPCG_OP_M5INV: apply5_full(st, P, fo, fi, h->mat(P, MAT_M5INV), vh, Ls, nullptr); break;
     case MSPCG_OP_MPHI: apply5_full(st, P, fo, fi, h->mat(P, MAT_MPHI), vh, Ls, nullptr); break;
-    case MSPCG_OP_D: h->D_op(st, P, fo, fi, "ap"); break;
-    case MSPCG_OP_DDAG: h->Ddag_op(st, P, fo, fi, "ap"); break;
-    case MSPCG_OP_A: h->A_op(st, P, fo, fi, "ap", nullptr); break;
     case MSPCG_OP_STORE: fo = fi; break;
     default: throw Error(MSPCG_ERR_INVALID_ARG, "unknown operator");
   }
