@@ -181,7 +181,7 @@ void ctl_after_update(hipStream_t st, const Ctl& c, double* scal, int n, const C
 //
 // Per-subdomain inner CG state: rho[d], alpha[d], beta[d], active[d].
 struct SubScalars {
-  double* rho;      // rho of the current iteration (and the one SUB_INIT / SUB_BETA write)
+  double* rho;      // rho of the current iteration
   double* alpha;
   double* beta;
   int* active;
@@ -189,33 +189,38 @@ struct SubScalars {
 };
 
 // Restrict the outer residual to the centre region of every subdomain:
-//   r_s = R_s r,  p_s = r_s,  t0 = E p_s (M_phi),  partial |r_s|^2 (per block, [d][bps])
+//   r_s = R_s r (also the first search direction p_s),  t0 = E p_s (M_phi),
+//   partial |r_s|^2 (per block, [d][bps])
 void sub_restrict(hipStream_t st, Prec outer, Prec inner, const FieldPtr& r_outer, const FieldPtr& rs,
-                  const FieldPtr& ps, const FieldPtr& t0, const void* E, const Lattice& lat, const SubTables& tc,
-                  int nsub, int Ls, double* partial, const Batch& bt = Batch());
-// alpha_d = rho_d / <p_s, q_s> from the [d][bps] partials pq (SUB_ALPHA, computed
-// by every wavefront), then z_s (+)= alpha_d p_s ; r_s -= alpha_d q_s ;
-// partial |r_s|^2  (first: z_s = alpha_d p_s).  last: the k-th step, whose
-// residual nothing reads: z_s only (r_s, q_s untouched, partials zero).
-void sub_update(hipStream_t st, Prec inner, const FieldPtr& zs, const FieldPtr& ps, const FieldPtr& rs,
-                const FieldPtr& qs, const SubScalars& sc, bool first, bool last, const SubTables& tc, int nsub,
-                int Ls, const double* pq, double* partial, const Batch& bt = Batch());
-// beta_d = |r_s|^2 / rho_d from the [d][bps] partials rr (SUB_BETA, computed by
-// every wavefront; rho_next = |r_s|^2), then p_s = r_s + beta_d p_s ; t0 = E p_s
-void sub_xpay5(hipStream_t st, Prec inner, const FieldPtr& ps, const FieldPtr& rs, const FieldPtr& t0,
-               const SubScalars& sc, const double* rr, const void* E, const SubTables& tc, int nsub, int Ls,
-               const Batch& bt = Batch());
-// z = sum_s R_s^T z_s (outer precision); partials Re<z, r>, Re<z, r_old> (r_old nullable)
+                  const FieldPtr& t0, const void* E, const Lattice& lat, const SubTables& tc, int nsub, int Ls,
+                  double* partial, const Batch& bt = Batch());
+// alpha_d = rho_d / <p_s, q_s> from the [d][bps] partials pq (computed by every
+// wavefront; 0 and inactive if <p_s, q_s> <= 0 or not finite), then r_out =
+// r_in - alpha_d q_s ; partial |r_out|^2.  With rr0 (the first step) rho_d is
+// the sum of the partials rr0 of |r_s|^2, active_d = rho_d > 0.
+void sub_update(hipStream_t st, Prec inner, const FieldPtr& rin, const FieldPtr& rout, const FieldPtr& qs,
+                const SubScalars& sc, const SubTables& tc, int nsub, int Ls, const double* pq, const double* rr0,
+                double* partial, const Batch& bt = Batch());
+// z_s (+)= alpha_d p_s with the alpha of sub_update (first: z_s = alpha_d p_s);
+// beta_d = |r_s|^2 / rho_d from the [d][bps] partials rr (computed by every
+// wavefront; rho_next = |r_s|^2), then p_s = r_s + beta_d p_s ; t0 = E p_s
+void sub_xpay5(hipStream_t st, Prec inner, const FieldPtr& ps, const FieldPtr& rs, const FieldPtr& zs,
+               const FieldPtr& t0, const SubScalars& sc, const double* rr, bool first, const void* E,
+               const SubTables& tc, int nsub, int Ls, const Batch& bt = Batch());
+// The last inner step, made by the prolongation: alpha_d as sub_update forms
+// it from pq (and rr0, when it is the only step: z_s = alpha_d p_s), z_s +=
+// alpha_d p_s in the inner storage.
+struct SubLast {
+  FieldPtr ps;
+  const double* pq;
+  const double* rr0;
+  SubScalars sc;
+};
+// z = sum_s R_s^T z_s (outer precision; z_s after `last` when given); partials
+// Re<z, r> (partial1, nullable), Re<z, r_old> (r_old nullable)
 void sub_prolong(hipStream_t st, Prec outer, Prec inner, const FieldPtr& z_outer, const FieldPtr& zs,
-                 const FieldPtr& r_outer, const FieldPtr* rold_outer, const Lattice& lat, const SubTables& tc,
-                 int nsub, int Ls, double* partial1, double* partial2, const Batch& bt = Batch());
-// per-subdomain scalar updates from [d][bps] partials:
-//   SUB_INIT : rho = S, active = rho > 0
-//   SUB_ALPHA: alpha = rho / S (0 and inactive if S <= 0 or not finite)
-//   SUB_BETA : if S == 0 inactive; beta = S / rho; rho = S
-enum SubFinish { SUB_INIT = 0, SUB_ALPHA, SUB_BETA };
-void sub_finish(hipStream_t st, const double* partial, int bps, int nsub, const SubScalars& sc, int mode,
-                const Batch& bt = Batch());
+                 const SubLast* last, const FieldPtr& r_outer, const FieldPtr* rold_outer, const Lattice& lat,
+                 const SubTables& tc, int nsub, int Ls, double* partial1, double* partial2, const Batch& bt = Batch());
 
 // ---------------------------------------------------------------- reduced-Ls preconditioner (reduced.hip)
 // out(x, so, mo, c) = sum_{si, mi} W[so][mo][si][mi] in(x, si, mi, c) (+ mu r(x, so, mo, c) when r

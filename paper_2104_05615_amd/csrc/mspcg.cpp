@@ -795,23 +795,28 @@ struct mspcg_ctx {
     sc.beta = buf("in.beta", (size_t)nb * nsub * sizeof(double)).as<double>();
     sc.active = buf("in.active", (size_t)nb * nsub * sizeof(int)).as<int>();
     const SubTables tc = tables(0, I);
-    double* prr = partial("in.rr", (int64_t)nb * nsub * tc.bps);
+    double* prr = partial("in.rr", (int64_t)nb * nsub * tc.bps);    // |r_s|^2 at the start
+    double* prr1 = partial("in.rr1", (int64_t)nb * nsub * tc.bps);  // and after a step
     double* ppap = partial("in.pap", (int64_t)nb * nsub * tc.bps);
-    sub_restrict(st, O, I, r, rs, ps, t0, mat(I, MAT_MPHI), lat, tc, nsub, Ls, prr, bt);
-    sub_finish(st, prr, tc.bps, nsub, sc, SUB_INIT, bt);
-    // the per-subdomain alpha and beta are formed inside the kernels that
-    // use them (sub_update, sub_xpay5) from the partials of the kernel
-    // before; rho alternates between two arrays so that no block of
-    // sub_xpay5 overwrites the rho another block still reads
+    // The first residual is the first search direction: it is stored once (in
+    // p) and the first update writes its residual to r.  The per-subdomain
+    // alpha and beta are formed inside the kernels that use them from the
+    // partials of the kernel before; rho alternates between two arrays so that
+    // no block of sub_xpay5 overwrites the rho another block still reads.  z is
+    // updated where p is read anyway: in sub_xpay5, the last step in the
+    // prolongation.
+    sub_restrict(st, O, I, r, ps, t0, mat(I, MAT_MPHI), lat, tc, nsub, Ls, prr, bt);
     for (int it = 0; it < k; ++it) {
       if (it > 0) {
-        sub_xpay5(st, I, ps, rs, t0, sc, prr, mat(I, MAT_MPHI), tc, nsub, Ls, bt);
+        sub_xpay5(st, I, ps, rs, zs, t0, sc, prr1, it == 1, mat(I, MAT_MPHI), tc, nsub, Ls, bt);
         std::swap(sc.rho, sc.rho_next);
       }
       Asub(st, I, qs, ps, t0, ppap, bt);
-      sub_update(st, I, zs, ps, rs, qs, sc, it == 0, it == k - 1, tc, nsub, Ls, ppap, prr, bt);
+      if (it < k - 1)
+        sub_update(st, I, it == 0 ? ps : rs, rs, qs, sc, tc, nsub, Ls, ppap, it == 0 ? prr : nullptr, prr1, bt);
     }
-    sub_prolong(st, O, I, z, zs, r, rold, lat, tc, nsub, Ls, pz1, pz2, bt);
+    const SubLast last{ps, ppap, k == 1 ? prr : nullptr, sc};
+    sub_prolong(st, O, I, z, zs, k > 0 ? &last : nullptr, r, rold, lat, tc, nsub, Ls, pz1, pz2, bt);
     ev_end(st, ev);
     return k;
   }
@@ -841,12 +846,11 @@ struct mspcg_ctx {
     const SubTables tc = tables(0, P);
     const int64_t nz = (int64_t)nsub * tc.bps;
     double* p1 = partial("ap.z1", nz);
-    double* p2 = partial("ap.z2", nz);
     const int64_t nc = (int64_t)nsub * nC;
-    FieldPtr rs = field("in.r", P, nc), ps = field("in.p", P, nc), t0 = field("in.t0", P, nc), qs = field("in.q", P, nc);
-    sub_restrict(st, O, P, fi, rs, ps, t0, mat(P, MAT_MPHI), lat, tc, nsub, Ls, p1);
+    FieldPtr ps = field("in.p", P, nc), t0 = field("in.t0", P, nc), qs = field("in.q", P, nc);
+    sub_restrict(st, O, P, fi, ps, t0, mat(P, MAT_MPHI), lat, tc, nsub, Ls, p1);
     Asub(st, P, qs, ps, t0, nullptr);
-    sub_prolong(st, O, P, fo, qs, fi, nullptr, lat, tc, nsub, Ls, p1, p2);
+    sub_prolong(st, O, P, fo, qs, nullptr, fi, nullptr, lat, tc, nsub, Ls, nullptr, nullptr);
   }
 };
 
@@ -1945,7 +1949,7 @@ int64_t estimate_solve_bytes(const mspcg_ctx* h, int nrhs) {
     const int64_t nc5 = (int64_t)h->nsub * h->nC * Ls;
     n += 5 * fbytes(I, nc5);
     n += fbytes(I, (int64_t)h->nsub * h->nN1 * Ls) + fbytes(I, (int64_t)h->nsub * h->nN2 * Ls);
-    parts += 4 * (int64_t)h->nsub * bps;
+    parts += 5 * (int64_t)h->nsub * bps;
     n += (int64_t)h->nsub * (4 * 8 + 4);   // rho (two arrays), alpha, beta, active
   } else {
     parts += 2 * nbl;
@@ -1970,10 +1974,7 @@ void apply_impl(mspcg_ctx* h, int op, Prec P, const double* in_dev, double* out_
     FieldPtr fi = h->field("ap.in", O, vh), fo = h->field("ap.out", O, vh);
     pack_field(st, fi, in_dev, vh, Ls);
     if (op == MSPCG_OP_PRECOND) {
-      const int64_t nz = h->precond_partials(O, P);
-      double* p1 = h->partial("ap.z1", nz);
-      double* p2 = h->partial("ap.z2", nz);
-      h->precondition(st, O, P, fo, fi, nullptr, h->sp.inner_iters, p1, p2);
+      h->precondition(st, O, P, fo, fi, nullptr, h->sp.inner_iters, nullptr, nullptr);
     } else {
       h->local_op(st, O, P, fo, fi);
     }

@@ -3,6 +3,14 @@
 // the inner CG's vector updates with per-subdomain scalars.  The four hops of
 // the local operator A_s run through hop_sub (kernels.hip).
 //
+// All of them are bound by the fields they stream (4.7 to 5.6 TB/s at 32^3x64;
+// a copy reaches 5.0), so the updates are grouped by what has to be read: a
+// middle inner step reads and writes 9 fields outside the hops (10 with z
+// updated beside r), the restriction writes r_s once (not as r_s and p_s), and
+// the last step's z goes from registers into the outer field.  Measured, the
+// whole preconditioner: 32^3x64 x 12, FP16, k = 3 19.2 -> 18.2 ms; 16^3x32 x
+// 12, FP16, k = 6 3081 -> 2999 us; 16^4 x 16, INT8, k = 6 1701 -> 1661 us.
+//
 // All kernels here map threads like the site kernels: a block owns ns sites
 // of C of one subdomain and all their Ls slices, so per-block partial sums are
 // grouped by subdomain as [d][bps].  Batched launches put the RHS in
@@ -54,14 +62,13 @@ __device__ __forceinline__ uint32_t c_global(const SubTables& tc, const Lattice&
 
 template <typename O, typename I>
 __global__ void __launch_bounds__(256)
-k_sub_restrict(Field<O> r, Field<I> rs, Field<I> ps, Field<I> t0, const calc_t<I>* E, Lattice lat, SubTables tc,
+k_sub_restrict(Field<O> r, Field<I> rs, Field<I> t0, const calc_t<I>* E, Lattice lat, SubTables tc,
                int Ls, int ns, double* partial, const int* mask) {
   using T = calc_t<I>;
   const int rhs = blockIdx.y;
   if (mask && mask[rhs] == 0) return;
   r = r.at(rhs);
   rs = rs.at(rhs);
-  ps = ps.at(rhs);
   t0 = t0.at(rhs);
   partial += (int64_t)rhs * gridDim.x;
   extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -75,7 +82,6 @@ k_sub_restrict(Field<O> r, Field<I> rs, Field<I> ps, Field<I> t0, const calc_t<I
     const int64_t g = c_global(tc, lat, c.d, c.j);
     load_site(r, g * Ls + c.s, v);
     store_site(rs, c.in5, v);
-    store_site(ps, c.in5, v);
   } else {
 #pragma unroll
     for (int k = 0; k < 24; ++k) v[k] = 0;
@@ -92,101 +98,127 @@ k_sub_restrict(Field<O> r, Field<I> rs, Field<I> ps, Field<I> t0, const calc_t<I
   if (threadIdx.x == 0) partial[c.blk] = tot;
 }
 
-// The scalar a k_sub_finish of mode SUB_ALPHA or SUB_BETA would compute for
-// subdomain d, evaluated in the kernel that uses it: every wavefront sums
-// the bps partials in k_sub_finish's fixed order (lane-strided, then a
-// butterfly), so each gets the same value to the bit without a barrier, and
-// the field loads of the kernel need not wait for it.  Thread 0 of the block
-// holding the subdomain's first site block also stores the new state (alpha
-// or beta, rho_next, active) as k_sub_finish does.  Other wavefronts may
-// read `active` while that thread clears it, but it is cleared only where
-// every reader takes the same decision from the same sum; rho is read from
-// one array and written to another.  Call from every lane of the wavefront.
-__device__ __forceinline__ double fused_finish(const double* partial, int bps, int64_t d, bool first_blk, int mode,
-                                               const double* rho, double* rho_next, double* alpha, double* beta,
-                                               int* active) {
-  const int lane = threadIdx.x & 63;
+// sum of the bps partials of subdomain d, by every wavefront in the same fixed
+// order (lane-strided, then a butterfly)
+__device__ __forceinline__ double sub_sum(const double* partial, int bps, int64_t d) {
   double S = 0;
-  for (int b = lane; b < bps; b += 64) S += partial[d * bps + b];
+  for (int b = threadIdx.x & 63; b < bps; b += 64) S += partial[d * bps + b];
   for (int off = 32; off > 0; off >>= 1) S += __shfl_xor(S, off);
-  const bool act = active[d] != 0;
-  const bool store = first_blk && threadIdx.x == 0;
-  double v;
-  if (mode == SUB_ALPHA) {
-    const bool ok = act && S > 0.0 && isfinite(S);
-    v = ok ? rho[d] / S : 0.0;
-    if (store) {
-      alpha[d] = v;
-      if (!ok) active[d] = 0;
-    }
-  } else {
-    const bool ok = act && S > 0.0;
-    v = ok ? S / rho[d] : 0.0;
-    if (store) {
-      beta[d] = v;
-      rho_next[d] = ok ? S : rho[d];
-      if (!ok) active[d] = 0;
+  return S;
+}
+
+// Per-subdomain scalars of the inner CG, evaluated in the kernel that uses
+// them: every wavefront sums the bps partials in one fixed order, so each gets
+// the same value to the bit without a barrier, and the field loads of the
+// kernel need not wait for it.  Thread 0 of the block holding the subdomain's
+// first site block also stores the new state.  Other wavefronts may read
+// `active` while that thread clears it, but it is cleared only where every
+// reader takes the same decision from the same sum; rho is read from one array
+// and written to another.  Call from every lane of the wavefront.
+//
+// alpha = rho / <p, q> (0 where the subdomain has stopped or <p, q> is not
+// positive).  With rr0 (the first step) rho is the sum of those partials of
+// |r_s|^2, and rho and active are stored too.
+__device__ __forceinline__ double fused_alpha(const double* pq, const double* rr0, int bps, int64_t d, bool first_blk,
+                                              double* rho, double* alpha, int* active) {
+  const double S = sub_sum(pq, bps, d);
+  const double r = rr0 ? sub_sum(rr0, bps, d) : rho[d];
+  const bool act = rr0 ? r > 0.0 : active[d] != 0;
+  const bool ok = act && S > 0.0 && isfinite(S);
+  const double v = ok ? r / S : 0.0;
+  if (first_blk && threadIdx.x == 0) {
+    alpha[d] = v;
+    if (rr0) {
+      rho[d] = r;
+      active[d] = ok ? 1 : 0;
+    } else if (!ok) {
+      active[d] = 0;
     }
   }
   return v;
 }
 
+// beta = |r_s|^2 / rho; rho_next = |r_s|^2
+__device__ __forceinline__ double fused_beta(const double* rr, int bps, int64_t d, bool first_blk, const double* rho,
+                                             double* rho_next, double* beta, int* active) {
+  const double S = sub_sum(rr, bps, d);
+  const bool ok = active[d] != 0 && S > 0.0;
+  const double v = ok ? S / rho[d] : 0.0;
+  if (first_blk && threadIdx.x == 0) {
+    beta[d] = v;
+    rho_next[d] = ok ? S : rho[d];
+    if (!ok) active[d] = 0;
+  }
+  return v;
+}
+
+// v = field[i] + coef x; v may be x.  A scaled format's value is its stored
+// number times its scale, and that product is the one that joins the addition
+// in the fused multiply-add; for FP16 component SWAP has them the other way
+// round.  All of it is written out because 16-bit storage turns one rounding
+// into another stored value: the preconditioner's output is what it was to the
+// bit when these updates were kernels of their own, contracted by the compiler.
+template <int SWAP, typename S, typename T>
+__device__ __forceinline__ void load_site_add(const Field<S>& f, uint32_t i, T coef, const T* x, T* v) {
+  T t[24];
+  if constexpr (StoreTraits<S>::scaled) {
+    const T sc = load_site_unscaled(f, i, t);
+#pragma unroll
+    for (int k = 0; k < 24; ++k)
+      v[k] = std::is_same<S, __half>::value && k == SWAP ? fmadd(coef, x[k], sc * t[k])
+                                                         : fmadd(sc, t[k], coef * x[k]);
+  } else {
+    load_site(f, i, t);
+#pragma unroll
+    for (int k = 0; k < 24; ++k) v[k] = fmadd(coef, x[k], t[k]);
+  }
+}
+
+// r_out = r_in - alpha q (the first step writes its residual to another buffer:
+// r_in stays as its search direction)
 template <typename I>
 __global__ void __launch_bounds__(256)
-k_sub_update(Field<I> zs, Field<I> ps, Field<I> rs, Field<I> qs, SubScalars sc, int nsub, int first, int last,
-             SubTables tc, int Ls, int ns, const double* pq, double* partial, const int* mask) {
+k_sub_update(Field<I> rin, Field<I> rout, Field<I> qs, SubScalars sc, int nsub, SubTables tc, int Ls, int ns,
+             const double* pq, const double* rr0, double* partial, const int* mask) {
   using T = calc_t<I>;
   __shared__ double red[16];
   const int rhs = blockIdx.y;
   if (mask && mask[rhs] == 0) return;
-  zs = zs.at(rhs);
-  ps = ps.at(rhs);
-  rs = rs.at(rhs);
+  rin = rin.at(rhs);
+  rout = rout.at(rhs);
   qs = qs.at(rhs);
   const int64_t so = (int64_t)rhs * nsub;
   partial += (int64_t)rhs * gridDim.x;
   const CSite c = c_site(tc, ns, Ls);
-  const double alpha_d = fused_finish(pq + so * tc.bps, tc.bps, c.d, c.blk == c.d * tc.bps, SUB_ALPHA, sc.rho + so,
-                                      nullptr, sc.alpha + so, nullptr, sc.active + so);
+  const double alpha_d = fused_alpha(pq + so * tc.bps, rr0 ? rr0 + so * tc.bps : nullptr, tc.bps, c.d,
+                                     c.blk == c.d * tc.bps, sc.rho + so, sc.alpha + so, sc.active + so);
   double loc = 0;
   if (c.valid) {
     const T a = (T)alpha_d;
-    T z[24], p[24];
-    load_site(ps, c.in5, p);
-    if (first) {
+    T r[24], q[24];
+    load_site(qs, c.in5, q);
+    load_site_add<6>(rin, c.in5, -a, q, r);
 #pragma unroll
-      for (int k = 0; k < 24; ++k) z[k] = a * p[k];
-    } else {
-      load_site(zs, c.in5, z);
-#pragma unroll
-      for (int k = 0; k < 24; ++k) z[k] += a * p[k];
-    }
-    store_site(zs, c.in5, z);
-    if (!last) {
-      T r[24], q[24];
-      load_site(rs, c.in5, r);
-      load_site(qs, c.in5, q);
-#pragma unroll
-      for (int k = 0; k < 24; ++k) {
-        r[k] -= a * q[k];
-        loc += (double)r[k] * (double)r[k];
-      }
-      store_site(rs, c.in5, r);
-    }
+    for (int k = 0; k < 24; ++k) loc += (double)r[k] * (double)r[k];
+    store_site(rout, c.in5, r);
   }
   const double tot = block_sum(loc, red);
   if (threadIdx.x == 0) partial[c.blk] = tot;
 }
 
+// z (+)= alpha p, p = r + beta p, t0 = E p.  The solution's update belongs to
+// the step before; it is made here, where p is read anyway (with the residual's
+// update it would read p once more).
 template <typename I>
 __global__ void __launch_bounds__(256)
-k_sub_xpay5(Field<I> ps, Field<I> rs, Field<I> t0, SubScalars sc, const double* rr, int nsub, const calc_t<I>* E,
-            SubTables tc, int Ls, int ns, const int* mask) {
+k_sub_xpay5(Field<I> ps, Field<I> rs, Field<I> zs, Field<I> t0, SubScalars sc, const double* rr, int nsub, int first,
+            const calc_t<I>* E, SubTables tc, int Ls, int ns, const int* mask) {
   using T = calc_t<I>;
   const int rhs = blockIdx.y;
   if (mask && mask[rhs] == 0) return;
   ps = ps.at(rhs);
   rs = rs.at(rhs);
+  zs = zs.at(rhs);
   t0 = t0.at(rhs);
   const int64_t so = (int64_t)rhs * nsub;
   extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -195,16 +227,21 @@ k_sub_xpay5(Field<I> ps, Field<I> rs, Field<I> t0, SubScalars sc, const double* 
   T* tile = mats + 2 * Ls * Ls;
   const CSite c = c_site(tc, ns, Ls);
   for (int k = threadIdx.x; k < 2 * Ls * Ls; k += blockDim.x) mats[k] = E[k];
-  const double beta_d = fused_finish(rr + so * tc.bps, tc.bps, c.d, c.blk == c.d * tc.bps, SUB_BETA, sc.rho + so,
-                                     sc.rho_next + so, nullptr, sc.beta + so, sc.active + so);
+  const double beta_d = fused_beta(rr + so * tc.bps, tc.bps, c.d, c.blk == c.d * tc.bps, sc.rho + so, sc.rho_next + so,
+                                   sc.beta + so, sc.active + so);
   T p[24];
   if (c.valid) {
-    const T b = (T)beta_d;
-    T r[24];
+    const T a = (T)sc.alpha[so + c.d], b = (T)beta_d;
+    T z[24];
     load_site(ps, c.in5, p);
-    load_site(rs, c.in5, r);
+    if (first) {
 #pragma unroll
-    for (int k = 0; k < 24; ++k) p[k] = r[k] + b * p[k];
+      for (int k = 0; k < 24; ++k) z[k] = a * p[k];
+    } else {
+      load_site_add<-1>(zs, c.in5, a, p, z);
+    }
+    store_site(zs, c.in5, z);
+    load_site_add<23>(rs, c.in5, b, p, p);
     store_site(ps, c.in5, p);
   } else {
 #pragma unroll
@@ -217,80 +254,108 @@ k_sub_xpay5(Field<I> ps, Field<I> rs, Field<I> t0, SubScalars sc, const double* 
   if (c.valid) store_site(t0, c.in5, p);
 }
 
+// v as a field of storage S holds it: the arithmetic of store_site and load_site
+template <typename S, typename T> __device__ __forceinline__ void as_stored(T* v) {
+  if constexpr (StoreTraits<S>::scaled) {
+    float mx = 0.f, tmp[24];
+#pragma unroll
+    for (int k = 0; k < 24; ++k) mx = fmaxf(mx, fabsf((float)v[k]));
+    if constexpr (std::is_same<S, int8_t>::value) {
+      const float inv = mx > 0.f ? 127.0f / mx : 0.f, sc = mx * (1.0f / 127.0f);
+#pragma unroll
+      for (int k = 0; k < 24; ++k) tmp[k] = (float)v[k] * inv;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const uint2 q = pack8_i8(tmp + 8 * k);
+        unpack8_i8(q, tmp + 8 * k);
+      }
+#pragma unroll
+      for (int k = 0; k < 24; ++k) v[k] = tmp[k] * sc;
+    } else {
+      const float inv = mx > 0.f ? 1.0f / mx : 0.f;
+#pragma unroll
+      for (int k = 0; k < 24; ++k) tmp[k] = (float)v[k] * inv;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const uint4 q = pack8<S>(tmp + 8 * k);
+        unpack8<S>(q, tmp + 8 * k);
+      }
+#pragma unroll
+      for (int k = 0; k < 24; ++k) v[k] = tmp[k] * mx;
+    }
+  }
+}
+
+// What the prolongation does to the inner solution first (pq set): the last
+// step's z (+)= alpha p, rounded to the inner storage as a store would.
+struct LastStep {
+  const double* pq;    // partials of <p, q>; null: zs is the solution
+  const double* rr0;   // partials of |r_s|^2 when there was one step only
+  int nsub, first;     // first: z = alpha p
+};
+
+// z = sum_s R_s^T z_s, with the partials of <z, r> and <z, r_old> when partial1
+// (partial2) is set
 template <typename O, typename I>
 __global__ void __launch_bounds__(256)
-k_sub_prolong(Field<O> z, Field<I> zs, Field<O> r, Field<O> rold, int has_rold, Lattice lat, SubTables tc, int Ls,
-              int ns, double* partial1, double* partial2, const int* mask) {
+k_sub_prolong(Field<O> z, Field<I> zs, Field<I> ps, LastStep ls, SubScalars sc, Field<O> r, Field<O> rold, Lattice lat,
+              SubTables tc, int Ls, int ns, double* partial1, double* partial2, const int* mask) {
   using T = calc_t<O>;
+  using TI = calc_t<I>;
   __shared__ double red[16];
   const int rhs = blockIdx.y;
   if (mask && mask[rhs] == 0) return;
   z = z.at(rhs);
   zs = zs.at(rhs);
+  ps = ps.at(rhs);
   r = r.at(rhs);
   rold = rold.at(rhs);
-  partial1 += (int64_t)rhs * gridDim.x;
-  if (partial2) partial2 += (int64_t)rhs * gridDim.x;
   const CSite c = c_site(tc, ns, Ls);
+  TI a = 0;
+  if (ls.pq) {
+    const int64_t so = (int64_t)rhs * ls.nsub;
+    a = (TI)fused_alpha(ls.pq + so * tc.bps, ls.rr0 ? ls.rr0 + so * tc.bps : nullptr, tc.bps, c.d,
+                        c.blk == c.d * tc.bps, sc.rho + so, sc.alpha + so, sc.active + so);
+  }
   double l1 = 0, l2 = 0;
   if (c.valid) {
     const int64_t g5 = c_global(tc, lat, c.d, c.j) * Ls + c.s;
-    T v[24], rv[24];
-    load_site(zs, c.in5, v);
-    store_site(z, g5, v);
-    // the dots use z as stored in the outer precision
-    load_site(z, g5, v);
-    load_site(r, g5, rv);
+    TI w[24];
+    if (ls.pq) {
+      TI p[24];
+      load_site(ps, c.in5, p);
+      if (ls.first) {
 #pragma unroll
-    for (int k = 0; k < 24; ++k) l1 += (double)v[k] * (double)rv[k];
-    if (has_rold) {
+        for (int k = 0; k < 24; ++k) w[k] = a * p[k];
+      } else {
+        load_site_add<-1>(zs, c.in5, a, p, w);
+      }
+      as_stored<I>(w);
+    } else {
+      load_site(zs, c.in5, w);
+    }
+    T v[24], rv[24];   // z in the outer precision, as stored
+#pragma unroll
+    for (int k = 0; k < 24; ++k) v[k] = (T)w[k];
+    store_site(z, g5, v);
+    if (partial1) {
+      load_site(r, g5, rv);
+#pragma unroll
+      for (int k = 0; k < 24; ++k) l1 += (double)v[k] * (double)rv[k];
+    }
+    if (partial2) {
       load_site(rold, g5, rv);
 #pragma unroll
       for (int k = 0; k < 24; ++k) l2 += (double)v[k] * (double)rv[k];
     }
   }
-  const double t1 = block_sum(l1, red);
-  if (threadIdx.x == 0) partial1[c.blk] = t1;
-  if (has_rold) {
-    const double t2 = block_sum(l2, red);
-    if (threadIdx.x == 0) partial2[c.blk] = t2;
+  if (partial1) {
+    const double t1 = block_sum(l1, red);
+    if (threadIdx.x == 0) partial1[(int64_t)rhs * gridDim.x + c.blk] = t1;
   }
-}
-
-// one wavefront per subdomain: lane l sums partials l, l+64, ... in order,
-// then a fixed butterfly over the 64 lanes -- deterministic
-__global__ void __launch_bounds__(64)
-k_sub_finish(const double* partial, int bps, int nsub, double* rho, double* alpha, double* beta, int* active,
-             int mode, const int* mask) {
-  const int d = blockIdx.x;
-  const int lane = threadIdx.x;
-  const int rhs = blockIdx.y;
-  if (mask && mask[rhs] == 0) return;
-  const int64_t so = (int64_t)rhs * nsub;
-  partial += so * bps;
-  rho += so;
-  alpha += so;
-  beta += so;
-  active += so;
-  double S = 0;
-  for (int b = lane; b < bps; b += 64) S += partial[(int64_t)d * bps + b];
-  for (int off = 32; off > 0; off >>= 1) S += __shfl_xor(S, off);
-  if (lane != 0 || d >= nsub) return;
-  switch (mode) {
-    case SUB_INIT:
-      rho[d] = S;
-      active[d] = S > 0.0 ? 1 : 0;
-      alpha[d] = 0.0;
-      beta[d] = 0.0;
-      break;
-    case SUB_ALPHA:
-      if (active[d] && S > 0.0 && isfinite(S)) alpha[d] = rho[d] / S;
-      else { alpha[d] = 0.0; active[d] = 0; }
-      break;
-    case SUB_BETA:
-      if (active[d] && S > 0.0) { beta[d] = S / rho[d]; rho[d] = S; }
-      else { beta[d] = 0.0; active[d] = 0; }
-      break;
+  if (partial2) {
+    const double t2 = block_sum(l2, red);
+    if (threadIdx.x == 0) partial2[(int64_t)rhs * gridDim.x + c.blk] = t2;
   }
 }
 
@@ -303,125 +368,129 @@ static dim3 c_grid(int nsub, const SubTables& tc, const Batch& bt) {
 }
 
 template <typename O, typename I>
-static void restrict_t(hipStream_t st, const FieldPtr& r, const FieldPtr& rs, const FieldPtr& ps, const FieldPtr& t0,
-                       const void* E, const Lattice& lat, const SubTables& tc, int nsub, int Ls, double* partial,
+static void restrict_t(hipStream_t st, const FieldPtr& r, const FieldPtr& rs, const FieldPtr& t0, const void* E,
+                       const Lattice& lat, const SubTables& tc, int nsub, int Ls, double* partial,
                        const Batch& bt) {
   using T = calc_t<I>;
   const int ns = c_ns(Ls, rs.prec);
   const size_t lds = 16 * sizeof(double) + sizeof(T) * (size_t)(2 * Ls * Ls + ns * tile_stride(Ls));
   hipLaunchKernelGGL((k_sub_restrict<O, I>), c_grid(nsub, tc, bt), dim3(site_block_threads(ns, Ls)), lds, st,
-                     typed<O>(r), typed<I>(rs), typed<I>(ps), typed<I>(t0), (const T*)E, lat, tc, Ls, ns, partial,
+                     typed<O>(r), typed<I>(rs), typed<I>(t0), (const T*)E, lat, tc, Ls, ns, partial,
                      bt.mask);
   LAUNCH_CHECK();
 }
 
 template <typename O>
-static void restrict_o(hipStream_t st, Prec inner, const FieldPtr& r, const FieldPtr& rs, const FieldPtr& ps,
-                       const FieldPtr& t0, const void* E, const Lattice& lat, const SubTables& tc, int nsub, int Ls,
+static void restrict_o(hipStream_t st, Prec inner, const FieldPtr& r, const FieldPtr& rs, const FieldPtr& t0,
+                       const void* E, const Lattice& lat, const SubTables& tc, int nsub, int Ls,
                        double* partial, const Batch& bt) {
   switch (inner) {
-    case Prec::F64: restrict_t<O, double>(st, r, rs, ps, t0, E, lat, tc, nsub, Ls, partial, bt); break;
-    case Prec::F32: restrict_t<O, float>(st, r, rs, ps, t0, E, lat, tc, nsub, Ls, partial, bt); break;
-    case Prec::F16: restrict_t<O, __half>(st, r, rs, ps, t0, E, lat, tc, nsub, Ls, partial, bt); break;
-    case Prec::BF16: restrict_t<O, __hip_bfloat16>(st, r, rs, ps, t0, E, lat, tc, nsub, Ls, partial, bt); break;
-    case Prec::I8: restrict_t<O, int8_t>(st, r, rs, ps, t0, E, lat, tc, nsub, Ls, partial, bt); break;
+    case Prec::F64: restrict_t<O, double>(st, r, rs, t0, E, lat, tc, nsub, Ls, partial, bt); break;
+    case Prec::F32: restrict_t<O, float>(st, r, rs, t0, E, lat, tc, nsub, Ls, partial, bt); break;
+    case Prec::F16: restrict_t<O, __half>(st, r, rs, t0, E, lat, tc, nsub, Ls, partial, bt); break;
+    case Prec::BF16: restrict_t<O, __hip_bfloat16>(st, r, rs, t0, E, lat, tc, nsub, Ls, partial, bt); break;
+    case Prec::I8: restrict_t<O, int8_t>(st, r, rs, t0, E, lat, tc, nsub, Ls, partial, bt); break;
   }
 }
 
 void sub_restrict(hipStream_t st, Prec outer, Prec inner, const FieldPtr& r_outer, const FieldPtr& rs,
-                  const FieldPtr& ps, const FieldPtr& t0, const void* E, const Lattice& lat, const SubTables& tc,
-                  int nsub, int Ls, double* partial, const Batch& bt) {
-  if (outer == Prec::F64) restrict_o<double>(st, inner, r_outer, rs, ps, t0, E, lat, tc, nsub, Ls, partial, bt);
-  else if (outer == Prec::F32) restrict_o<float>(st, inner, r_outer, rs, ps, t0, E, lat, tc, nsub, Ls, partial, bt);
+                  const FieldPtr& t0, const void* E, const Lattice& lat, const SubTables& tc, int nsub, int Ls,
+                  double* partial, const Batch& bt) {
+  if (outer == Prec::F64) restrict_o<double>(st, inner, r_outer, rs, t0, E, lat, tc, nsub, Ls, partial, bt);
+  else if (outer == Prec::F32) restrict_o<float>(st, inner, r_outer, rs, t0, E, lat, tc, nsub, Ls, partial, bt);
   else throw std::runtime_error("sub_restrict: outer precision must be FP64 or FP32");
 }
 
 template <typename I>
-static void update_t(hipStream_t st, const FieldPtr& zs, const FieldPtr& ps, const FieldPtr& rs, const FieldPtr& qs,
-                     const SubScalars& sc, bool first, bool last, const SubTables& tc, int nsub, int Ls,
-                     const double* pq, double* partial, const Batch& bt) {
-  const int ns = c_ns(Ls, zs.prec);
-  hipLaunchKernelGGL((k_sub_update<I>), c_grid(nsub, tc, bt), dim3(site_block_threads(ns, Ls)), 0, st, typed<I>(zs),
-                     typed<I>(ps), typed<I>(rs), typed<I>(qs), sc, nsub, first ? 1 : 0, last ? 1 : 0, tc, Ls, ns, pq,
-                     partial, bt.mask);
+static void update_t(hipStream_t st, const FieldPtr& rin, const FieldPtr& rout, const FieldPtr& qs,
+                     const SubScalars& sc, const SubTables& tc, int nsub, int Ls, const double* pq, const double* rr0,
+                     double* partial, const Batch& bt) {
+  const int ns = c_ns(Ls, rin.prec);
+  hipLaunchKernelGGL((k_sub_update<I>), c_grid(nsub, tc, bt), dim3(site_block_threads(ns, Ls)), 0, st, typed<I>(rin),
+                     typed<I>(rout), typed<I>(qs), sc, nsub, tc, Ls, ns, pq, rr0, partial, bt.mask);
   LAUNCH_CHECK();
 }
 
-void sub_update(hipStream_t st, Prec inner, const FieldPtr& zs, const FieldPtr& ps, const FieldPtr& rs,
-                const FieldPtr& qs, const SubScalars& sc, bool first, bool last, const SubTables& tc, int nsub,
-                int Ls, const double* pq, double* partial, const Batch& bt) {
+void sub_update(hipStream_t st, Prec inner, const FieldPtr& rin, const FieldPtr& rout, const FieldPtr& qs,
+                const SubScalars& sc, const SubTables& tc, int nsub, int Ls, const double* pq, const double* rr0,
+                double* partial, const Batch& bt) {
   switch (inner) {
-    case Prec::F64: update_t<double>(st, zs, ps, rs, qs, sc, first, last, tc, nsub, Ls, pq, partial, bt); break;
-    case Prec::F32: update_t<float>(st, zs, ps, rs, qs, sc, first, last, tc, nsub, Ls, pq, partial, bt); break;
-    case Prec::F16: update_t<__half>(st, zs, ps, rs, qs, sc, first, last, tc, nsub, Ls, pq, partial, bt); break;
-    case Prec::BF16: update_t<__hip_bfloat16>(st, zs, ps, rs, qs, sc, first, last, tc, nsub, Ls, pq, partial, bt); break;
-    case Prec::I8: update_t<int8_t>(st, zs, ps, rs, qs, sc, first, last, tc, nsub, Ls, pq, partial, bt); break;
+    case Prec::F64: update_t<double>(st, rin, rout, qs, sc, tc, nsub, Ls, pq, rr0, partial, bt); break;
+    case Prec::F32: update_t<float>(st, rin, rout, qs, sc, tc, nsub, Ls, pq, rr0, partial, bt); break;
+    case Prec::F16: update_t<__half>(st, rin, rout, qs, sc, tc, nsub, Ls, pq, rr0, partial, bt); break;
+    case Prec::BF16: update_t<__hip_bfloat16>(st, rin, rout, qs, sc, tc, nsub, Ls, pq, rr0, partial, bt); break;
+    case Prec::I8: update_t<int8_t>(st, rin, rout, qs, sc, tc, nsub, Ls, pq, rr0, partial, bt); break;
   }
 }
 
 template <typename I>
-static void xpay5_t(hipStream_t st, const FieldPtr& ps, const FieldPtr& rs, const FieldPtr& t0, const SubScalars& sc,
-                    const double* rr, const void* E, const SubTables& tc, int nsub, int Ls, const Batch& bt) {
+static void xpay5_t(hipStream_t st, const FieldPtr& ps, const FieldPtr& rs, const FieldPtr& zs, const FieldPtr& t0,
+                    const SubScalars& sc, const double* rr, bool first, const void* E, const SubTables& tc, int nsub,
+                    int Ls, const Batch& bt) {
   using T = calc_t<I>;
   const int ns = c_ns(Ls, ps.prec);
   const size_t lds = 16 * sizeof(double) + sizeof(T) * (size_t)(2 * Ls * Ls + ns * tile_stride(Ls));
   hipLaunchKernelGGL((k_sub_xpay5<I>), c_grid(nsub, tc, bt), dim3(site_block_threads(ns, Ls)), lds, st, typed<I>(ps),
-                     typed<I>(rs), typed<I>(t0), sc, rr, nsub, (const T*)E, tc, Ls, ns, bt.mask);
+                     typed<I>(rs), typed<I>(zs), typed<I>(t0), sc, rr, nsub, first ? 1 : 0, (const T*)E, tc, Ls, ns,
+                     bt.mask);
   LAUNCH_CHECK();
 }
 
-void sub_xpay5(hipStream_t st, Prec inner, const FieldPtr& ps, const FieldPtr& rs, const FieldPtr& t0,
-               const SubScalars& sc, const double* rr, const void* E, const SubTables& tc, int nsub, int Ls,
-               const Batch& bt) {
+void sub_xpay5(hipStream_t st, Prec inner, const FieldPtr& ps, const FieldPtr& rs, const FieldPtr& zs,
+               const FieldPtr& t0, const SubScalars& sc, const double* rr, bool first, const void* E,
+               const SubTables& tc, int nsub, int Ls, const Batch& bt) {
   switch (inner) {
-    case Prec::F64: xpay5_t<double>(st, ps, rs, t0, sc, rr, E, tc, nsub, Ls, bt); break;
-    case Prec::F32: xpay5_t<float>(st, ps, rs, t0, sc, rr, E, tc, nsub, Ls, bt); break;
-    case Prec::F16: xpay5_t<__half>(st, ps, rs, t0, sc, rr, E, tc, nsub, Ls, bt); break;
-    case Prec::BF16: xpay5_t<__hip_bfloat16>(st, ps, rs, t0, sc, rr, E, tc, nsub, Ls, bt); break;
-    case Prec::I8: xpay5_t<int8_t>(st, ps, rs, t0, sc, rr, E, tc, nsub, Ls, bt); break;
+    case Prec::F64: xpay5_t<double>(st, ps, rs, zs, t0, sc, rr, first, E, tc, nsub, Ls, bt); break;
+    case Prec::F32: xpay5_t<float>(st, ps, rs, zs, t0, sc, rr, first, E, tc, nsub, Ls, bt); break;
+    case Prec::F16: xpay5_t<__half>(st, ps, rs, zs, t0, sc, rr, first, E, tc, nsub, Ls, bt); break;
+    case Prec::BF16: xpay5_t<__hip_bfloat16>(st, ps, rs, zs, t0, sc, rr, first, E, tc, nsub, Ls, bt); break;
+    case Prec::I8: xpay5_t<int8_t>(st, ps, rs, zs, t0, sc, rr, first, E, tc, nsub, Ls, bt); break;
   }
 }
 
 template <typename O, typename I>
-static void prolong_t(hipStream_t st, const FieldPtr& z, const FieldPtr& zs, const FieldPtr& r, const FieldPtr* rold,
-                      const Lattice& lat, const SubTables& tc, int nsub, int Ls, double* p1, double* p2,
-                      const Batch& bt) {
+static void prolong_t(hipStream_t st, const FieldPtr& z, const FieldPtr& zs, const SubLast* last, const FieldPtr& r,
+                      const FieldPtr* rold, const Lattice& lat, const SubTables& tc, int nsub, int Ls, double* p1,
+                      double* p2, const Batch& bt) {
   const int ns = c_ns(Ls, zs.prec);
   Field<O> ro = rold ? typed<O>(*rold) : Field<O>{};
+  LastStep ls{nullptr, nullptr, nsub, 0};
+  Field<I> ps{};
+  SubScalars sc{};
+  if (last) {
+    ls.pq = last->pq;
+    ls.rr0 = last->rr0;
+    ls.first = last->rr0 ? 1 : 0;
+    ps = typed<I>(last->ps);
+    sc = last->sc;
+  }
   hipLaunchKernelGGL((k_sub_prolong<O, I>), c_grid(nsub, tc, bt), dim3(site_block_threads(ns, Ls)), 0, st,
-                     typed<O>(z), typed<I>(zs), typed<O>(r), ro, rold ? 1 : 0, lat, tc, Ls, ns, p1,
+                     typed<O>(z), typed<I>(zs), ps, ls, sc, typed<O>(r), ro, lat, tc, Ls, ns, p1,
                      rold ? p2 : nullptr, bt.mask);
   LAUNCH_CHECK();
 }
 
 template <typename O>
-static void prolong_o(hipStream_t st, Prec inner, const FieldPtr& z, const FieldPtr& zs, const FieldPtr& r,
-                      const FieldPtr* rold, const Lattice& lat, const SubTables& tc, int nsub, int Ls, double* p1,
-                      double* p2, const Batch& bt) {
+static void prolong_o(hipStream_t st, Prec inner, const FieldPtr& z, const FieldPtr& zs, const SubLast* last,
+                      const FieldPtr& r, const FieldPtr* rold, const Lattice& lat, const SubTables& tc, int nsub,
+                      int Ls, double* p1, double* p2, const Batch& bt) {
   switch (inner) {
-    case Prec::F64: prolong_t<O, double>(st, z, zs, r, rold, lat, tc, nsub, Ls, p1, p2, bt); break;
-    case Prec::F32: prolong_t<O, float>(st, z, zs, r, rold, lat, tc, nsub, Ls, p1, p2, bt); break;
-    case Prec::F16: prolong_t<O, __half>(st, z, zs, r, rold, lat, tc, nsub, Ls, p1, p2, bt); break;
-    case Prec::BF16: prolong_t<O, __hip_bfloat16>(st, z, zs, r, rold, lat, tc, nsub, Ls, p1, p2, bt); break;
-    case Prec::I8: prolong_t<O, int8_t>(st, z, zs, r, rold, lat, tc, nsub, Ls, p1, p2, bt); break;
+    case Prec::F64: prolong_t<O, double>(st, z, zs, last, r, rold, lat, tc, nsub, Ls, p1, p2, bt); break;
+    case Prec::F32: prolong_t<O, float>(st, z, zs, last, r, rold, lat, tc, nsub, Ls, p1, p2, bt); break;
+    case Prec::F16: prolong_t<O, __half>(st, z, zs, last, r, rold, lat, tc, nsub, Ls, p1, p2, bt); break;
+    case Prec::BF16: prolong_t<O, __hip_bfloat16>(st, z, zs, last, r, rold, lat, tc, nsub, Ls, p1, p2, bt); break;
+    case Prec::I8: prolong_t<O, int8_t>(st, z, zs, last, r, rold, lat, tc, nsub, Ls, p1, p2, bt); break;
   }
 }
 
 void sub_prolong(hipStream_t st, Prec outer, Prec inner, const FieldPtr& z_outer, const FieldPtr& zs,
-                 const FieldPtr& r_outer, const FieldPtr* rold_outer, const Lattice& lat, const SubTables& tc,
-                 int nsub, int Ls, double* partial1, double* partial2, const Batch& bt) {
-  if (outer == Prec::F64) prolong_o<double>(st, inner, z_outer, zs, r_outer, rold_outer, lat, tc, nsub, Ls, partial1,
-                                            partial2, bt);
-  else if (outer == Prec::F32) prolong_o<float>(st, inner, z_outer, zs, r_outer, rold_outer, lat, tc, nsub, Ls,
+                 const SubLast* last, const FieldPtr& r_outer, const FieldPtr* rold_outer, const Lattice& lat,
+                 const SubTables& tc, int nsub, int Ls, double* partial1, double* partial2, const Batch& bt) {
+  if (outer == Prec::F64) prolong_o<double>(st, inner, z_outer, zs, last, r_outer, rold_outer, lat, tc, nsub, Ls,
+                                            partial1, partial2, bt);
+  else if (outer == Prec::F32) prolong_o<float>(st, inner, z_outer, zs, last, r_outer, rold_outer, lat, tc, nsub, Ls,
                                                 partial1, partial2, bt);
   else throw std::runtime_error("sub_prolong: outer precision must be FP64 or FP32");
-}
-
-void sub_finish(hipStream_t st, const double* partial, int bps, int nsub, const SubScalars& sc, int mode,
-                const Batch& bt) {
-  hipLaunchKernelGGL(k_sub_finish, dim3((unsigned)nsub, (unsigned)bt.n), dim3(64), 0, st, partial, bps, nsub, sc.rho,
-                     sc.alpha, sc.beta, sc.active, mode, bt.mask);
-  LAUNCH_CHECK();
 }
 
 }  // namespace mspcg
