@@ -88,21 +88,35 @@ static HopWork hop_work(int64_t nblk, const Batch& bt, const Sched& sc) {
 // The wavefront-per-16-sites kernel serves subdomain hops with Ls a multiple
 // of 4 (up to 16) in FP32, FP16 and INT8 storage, where the MFMA epilogue is
 // on: the non-adjoint hops h1 and h2, whose output regions grow past their
-// input so that many sites lack some of the eight terms, and the 8-bit
-// format's adjoint ones.  Measured per launch, general kernel -> this one:
-//   16^3x32 x 12, FP16, 4^3x8: h1 81 -> 74, h2 211 -> 160 us (h3 122 -> 132,
+// input so that many sites lack some of the eight terms, and adjoint ones up
+// to the Ls below.  Measured per launch, general kernel -> this one, us:
+//   16^3x32 x 12, FP16, 4^3x8: h1 81 -> 74, h2 211 -> 160 (h3 122 -> 132,
 //     h4 69 -> 69); 32^3x64 x 12, FP16, 8^3x16: h1 951 -> 847, h2 1867 -> 1542
-//     (h3 1162 -> 1227, h4 852 -> 901)
+//     (h3 1157 -> 1222, h4 848 -> 899); 16^4 x 16, FP16, 12 RHS (h3 589 -> 608)
+//   16^4 x 8, FP16, 4^4: h3 46 -> 40, h4 35 -> 28; 8^4 x 8: h3 11.2 -> 10.2,
+//     h4 13.2 -> 13.0
 //   16^4 x 8, FP32, 4^4: h1 57 -> 57, h2 163 -> 114 (h3 89 -> 104, h4 50 -> 54)
 //   16^4 x 16, INT8, 4^4: h1 59 -> 47, h2 160 -> 96, h3 67 -> 63, h4 44 -> 34
-// In h3 and h4 every site has all eight terms and the general kernel's three
-// or four wavefronts per 16 sites keep more of the neighbours in L1.
+// In h3 and h4 every site has all eight terms: there the general kernel's
+// three or four wavefronts per 16 sites (Ls 12 and 16) keep more of the
+// neighbours in L1, while with two (Ls 8) or one its workgroups' barriers and
+// tiles cost more than that.
 template <typename Geo, typename S> struct WaveHops {
-  static constexpr bool plain = false, adjoint = false;
+  static constexpr bool plain = false;
+  static constexpr int adjoint_ls = 0;   // adjoint hops up to this Ls
 };
-template <> struct WaveHops<SubGeo<float, float>, float> { static constexpr bool plain = true, adjoint = false; };
-template <> struct WaveHops<SubGeo<float, __half, true>, __half> { static constexpr bool plain = true, adjoint = false; };
-template <> struct WaveHops<SubGeo<float, __half, true>, int8_t> { static constexpr bool plain = true, adjoint = true; };
+template <> struct WaveHops<SubGeo<float, float>, float> {
+  static constexpr bool plain = true;
+  static constexpr int adjoint_ls = 0;
+};
+template <> struct WaveHops<SubGeo<float, __half, true>, __half> {
+  static constexpr bool plain = true;
+  static constexpr int adjoint_ls = 8;
+};
+template <> struct WaveHops<SubGeo<float, __half, true>, int8_t> {
+  static constexpr bool plain = true;
+  static constexpr int adjoint_ls = 16;
+};
 
 template <typename Geo, typename S, int LC, bool DAG>
 static void launch_hop_wave_lc(hipStream_t st, const Geo& geo, dim3 grid, Field<S> out, Field<S> in, bool has_w,
@@ -119,11 +133,15 @@ template <typename Geo, typename S, bool DAG>
 static void launch_hop_wave(hipStream_t st, const Geo& geo, dim3 grid, Field<S> out, Field<S> in, bool has_w,
                             Field<S> wf, Field<S> df, int Ls, const float* E0, const float* E1, double* dot,
                             const HopWork& wk) {
+  constexpr int max_lc = (DAG ? WaveHops<Geo, S>::adjoint_ls : 16) / 4;
   switch (Ls / 4) {
     case 1: launch_hop_wave_lc<Geo, S, 1, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk); break;
     case 2: launch_hop_wave_lc<Geo, S, 2, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk); break;
-    case 3: launch_hop_wave_lc<Geo, S, 3, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk); break;
-    default: launch_hop_wave_lc<Geo, S, 4, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk); break;
+    default:
+      if constexpr (max_lc > 2) {
+        if (Ls == 12) launch_hop_wave_lc<Geo, S, 3, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk);
+        else launch_hop_wave_lc<Geo, S, 4, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk);
+      }
   }
 }
 
@@ -144,8 +162,8 @@ static void launch_hop_mf(hipStream_t st, const Geo& geo, int64_t nblocks, const
   dim3 grid((unsigned)(nblocks * bt.n)), block(site_block_threads(ns, Ls));
   const int wid = epi.w_identity ? 1 : 0;
   if constexpr (MF && WaveHops<Geo, S>::plain) {
-    if (Ls % 4 == 0 && E1 && (!w || tileB) && !(dagger && !WaveHops<Geo, S>::adjoint)) {
-      if constexpr (WaveHops<Geo, S>::adjoint) {
+    if (Ls % 4 == 0 && E1 && (!w || tileB) && !(dagger && Ls > WaveHops<Geo, S>::adjoint_ls)) {
+      if constexpr (WaveHops<Geo, S>::adjoint_ls > 0) {
         if (dagger) {
           launch_hop_wave<Geo, S, true>(st, geo, grid, typed<S>(out), typed<S>(in), w != nullptr, wf, df, Ls, E0, E1,
                                         epi.dot_partial, wk);
