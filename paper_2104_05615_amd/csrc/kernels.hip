@@ -88,35 +88,55 @@ static HopWork hop_work(int64_t nblk, const Batch& bt, const Sched& sc) {
 // The wavefront-per-16-sites kernel serves subdomain hops with Ls a multiple
 // of 4 (up to 16) in FP32, FP16 and INT8 storage, where the MFMA epilogue is
 // on: the non-adjoint hops h1 and h2, whose output regions grow past their
-// input so that many sites lack some of the eight terms, and adjoint ones up
-// to the Ls below.  Measured per launch, general kernel -> this one, us:
-//   16^3x32 x 12, FP16, 4^3x8: h1 81 -> 74, h2 211 -> 160 (h3 122 -> 132,
+// input so that many sites lack some of the eight terms, and the 8-bit
+// format's adjoint ones.  Measured per launch, general kernel -> this one:
+//   16^3x32 x 12, FP16, 4^3x8: h1 81 -> 74, h2 211 -> 160 us (h3 122 -> 132,
 //     h4 69 -> 69); 32^3x64 x 12, FP16, 8^3x16: h1 951 -> 847, h2 1867 -> 1542
-//     (h3 1157 -> 1222, h4 848 -> 899); 16^4 x 16, FP16, 12 RHS (h3 589 -> 608)
-//   16^4 x 8, FP16, 4^4: h3 46 -> 40, h4 35 -> 28; 8^4 x 8: h3 11.2 -> 10.2,
-//     h4 13.2 -> 13.0
+//     (h3 1157 -> 1222, h4 848 -> 899)
 //   16^4 x 8, FP32, 4^4: h1 57 -> 57, h2 163 -> 114 (h3 89 -> 104, h4 50 -> 54)
 //   16^4 x 16, INT8, 4^4: h1 59 -> 47, h2 160 -> 96, h3 67 -> 63, h4 44 -> 34
-// In h3 and h4 every site has all eight terms: there the general kernel's
-// three or four wavefronts per 16 sites (Ls 12 and 16) keep more of the
-// neighbours in L1, while with two (Ls 8) or one its workgroups' barriers and
-// tiles cost more than that.
+// In h3 and h4 every site has all eight terms and the general kernel's three
+// or four wavefronts per 16 sites keep more of the neighbours in L1.
 template <typename Geo, typename S> struct WaveHops {
-  static constexpr bool plain = false;
-  static constexpr int adjoint_ls = 0;   // adjoint hops up to this Ls
+  static constexpr bool plain = false, adjoint = false;
 };
-template <> struct WaveHops<SubGeo<float, float>, float> {
-  static constexpr bool plain = true;
-  static constexpr int adjoint_ls = 0;
-};
-template <> struct WaveHops<SubGeo<float, __half, true>, __half> {
-  static constexpr bool plain = true;
-  static constexpr int adjoint_ls = 8;
-};
-template <> struct WaveHops<SubGeo<float, __half, true>, int8_t> {
-  static constexpr bool plain = true;
-  static constexpr int adjoint_ls = 16;
-};
+template <> struct WaveHops<SubGeo<float, float>, float> { static constexpr bool plain = true, adjoint = false; };
+template <> struct WaveHops<SubGeo<float, __half, true>, __half> { static constexpr bool plain = true, adjoint = false; };
+template <> struct WaveHops<SubGeo<float, __half, true>, int8_t> { static constexpr bool plain = true, adjoint = true; };
+
+// The lane-per-5D-site kernel serves the 16- and 8-bit formats' subdomain hops
+// with Ls 4, 8 or 16 before both: launches of up to 3072 wavefronts (three per
+// SIMD), where the time is one wavefront's chain, and at every size those hops
+// that its epilogue without redistribution makes faster.  Measured per launch,
+// us, the other kernels -> this one:
+//   wavefronts, FP16, Ls 8: 512 (h4) 13.0 -> 8.9; 768 (h1) 9.6 -> 8.7; 1664 (h2)
+//     12.1 -> 9.9; 3328 (h2) 15.6 -> 15.6; 3840 (h2) 19.2 -> 21.3; Ls 16: 1536
+//     (h1) 12.6 -> 9.6; 2624 (h3) 23.7 -> 22.6; 4480 (h1) 18.9 -> 21.9
+//   FP16 h4: 16^4 x 16, 4^4 52.8 -> 40.4; 24^3x48 x 4, 6^3x12 137 -> 117;
+//     32^3x64 x 8, 8^3x16 623 -> 579, x 16 1196 -> 1129
+//   FP16 h3: 24^3x48 x 4 199 -> 192, x 8 314 -> 295; 32^3x64 x 8 825 -> 806
+//     (x 16 1432 -> 1603)
+//   INT8, 24^3x48 x 4: h1 127 -> 111, h2 242 -> 211, h3 169 -> 146, h4 126 -> 100;
+//     x 8: h3 248 -> 225 (h1 178 -> 186, h2 351 -> 371, h4 164 -> 168)
+// In the rest the link that the wavefront kernel loads once per Ls / 4 slices,
+// or the general kernel's reuse of neighbours in L1, weighs more.
+template <typename S> static bool lane_hop(int Ls, bool dagger, bool has_w, int64_t nblk) {
+  if (Ls != 4 && Ls != 8 && Ls != 16) return false;
+  if (nblk * (Ls / 4) <= 3072) return true;
+  if (std::is_same<S, int8_t>::value) return Ls == 4 || (Ls == 8 && dagger && !has_w);
+  return dagger && (has_w || Ls <= 8);
+}
+
+template <typename Geo, typename S, int Ls, bool DAG>
+static void launch_hop_lane(hipStream_t st, const Geo& geo, dim3 grid, Field<S> out, Field<S> in, bool has_w,
+                            Field<S> wf, Field<S> df, const float* E0, const float* E1, double* dot,
+                            const HopWork& wk) {
+  const dim3 block(16 * Ls);
+  if (has_w) hipLaunchKernelGGL((k_hop_lane<Geo, S, Ls, DAG, true>), grid, block, 0, st, geo, out, in, wf, df, E0, E1,
+                                dot, wk);
+  else hipLaunchKernelGGL((k_hop_lane<Geo, S, Ls, DAG, false>), grid, block, 0, st, geo, out, in, wf, df, E0, E1, dot,
+                          wk);
+}
 
 template <typename Geo, typename S, int LC, bool DAG>
 static void launch_hop_wave_lc(hipStream_t st, const Geo& geo, dim3 grid, Field<S> out, Field<S> in, bool has_w,
@@ -133,15 +153,14 @@ template <typename Geo, typename S, bool DAG>
 static void launch_hop_wave(hipStream_t st, const Geo& geo, dim3 grid, Field<S> out, Field<S> in, bool has_w,
                             Field<S> wf, Field<S> df, int Ls, const float* E0, const float* E1, double* dot,
                             const HopWork& wk) {
-  constexpr int max_lc = (DAG ? WaveHops<Geo, S>::adjoint_ls : 16) / 4;
   switch (Ls / 4) {
-    case 1: launch_hop_wave_lc<Geo, S, 1, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk); break;
+    case 1:
+      if constexpr (!std::is_same<S, int8_t>::value)   // INT8 with Ls 4: lane_hop
+        launch_hop_wave_lc<Geo, S, 1, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk);
+      break;
     case 2: launch_hop_wave_lc<Geo, S, 2, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk); break;
-    default:
-      if constexpr (max_lc > 2) {
-        if (Ls == 12) launch_hop_wave_lc<Geo, S, 3, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk);
-        else launch_hop_wave_lc<Geo, S, 4, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk);
-      }
+    case 3: launch_hop_wave_lc<Geo, S, 3, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk); break;
+    default: launch_hop_wave_lc<Geo, S, 4, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk); break;
   }
 }
 
@@ -161,9 +180,26 @@ static void launch_hop_mf(hipStream_t st, const Geo& geo, int64_t nblocks, const
   const HopWork wk = hop_work(nblocks, bt, sc);
   dim3 grid((unsigned)(nblocks * bt.n)), block(site_block_threads(ns, Ls));
   const int wid = epi.w_identity ? 1 : 0;
+  if constexpr (MF && WaveHops<Geo, S>::plain && sizeof(S) < 4) {
+    if (E1 && (!w || tileB) && lane_hop<S>(Ls, dagger, w != nullptr, nblocks * bt.n)) {
+      auto go = [&](auto lc, auto dag) {
+        launch_hop_lane<Geo, S, decltype(lc)::value, decltype(dag)::value>(
+            st, geo, grid, typed<S>(out), typed<S>(in), w != nullptr, wf, df, E0, E1, epi.dot_partial, wk);
+      };
+      auto by_ls = [&](auto dag) {
+        if (Ls == 4) go(std::integral_constant<int, 4>(), dag);
+        else if (Ls == 8) go(std::integral_constant<int, 8>(), dag);
+        else go(std::integral_constant<int, 16>(), dag);
+      };
+      if (dagger) by_ls(std::true_type());
+      else by_ls(std::false_type());
+      LAUNCH_CHECK();
+      return;
+    }
+  }
   if constexpr (MF && WaveHops<Geo, S>::plain) {
-    if (Ls % 4 == 0 && E1 && (!w || tileB) && !(dagger && Ls > WaveHops<Geo, S>::adjoint_ls)) {
-      if constexpr (WaveHops<Geo, S>::adjoint_ls > 0) {
+    if (Ls % 4 == 0 && E1 && (!w || tileB) && !(dagger && !WaveHops<Geo, S>::adjoint)) {
+      if constexpr (WaveHops<Geo, S>::adjoint) {
         if (dagger) {
           launch_hop_wave<Geo, S, true>(st, geo, grid, typed<S>(out), typed<S>(in), w != nullptr, wf, df, Ls, E0, E1,
                                         epi.dot_partial, wk);

@@ -1,6 +1,6 @@
 // One hop with the fused fifth-dimension epilogue, a wavefront per 16 output
-// sites (the general kernel is k_hop in sitekern.h; results are the same bit
-// for bit).
+// sites, or (at the end) a lane per 5D output site.  The general kernel is
+// k_hop in sitekern.h; results are the same bit for bit.
 //
 // For Ls = 4 LC <= 16 a wavefront owns 16 sites x Ls slices by itself: lane
 // 4 j + g works on the slices s = 4 r + g, r < LC, of site j.  The four lanes
@@ -625,6 +625,224 @@ k_hop_wave(Geo geo, Field<S> out_b, Field<S> in_b, Field<S> w_b, Field<S> dotf_b
         }
         const double tot = wave_dot<LC>(buf, lane);
         if (lane == 0) dot_partial[(int64_t)rhs * wk.nblk + blk] = tot;
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------- small launches
+
+// The same hop with a wavefront per 64 / Ls sites, a lane per 5D site, for the
+// 16- and 8-bit formats and Ls = 4, 8 or 16.  A workgroup has the wavefronts of
+// 16 sites; they meet only in the sum of the dot.
+//
+// What bounds it: the length of one wavefront's instruction and memory chain,
+// in launches that give each SIMD about one wavefront.  So all loads of the hop
+// are in flight at once (a lane has one slice, hence registers for eight
+// terms), with those of the centre field, the dot and the matrices behind them;
+// and the epilogue's MFMAs have 4 sites x 4 components as rows and slices as
+// columns, one group of 4 sites after the other (each in its part of the k
+// range), so a lane ends with the 24 components of the 5D site that it began
+// with and stores them from its registers.  At 8^4 x 8, FP16, 16 subdomains of
+// 4^4, h4 as the wavefront kernel spent 2000 of 21000 cycles on its tables,
+// 7000 on the hop, 2000 waiting for the centre field, 3100 on the products and
+// 7000 on packing and the dot; per launch h1 9.6 -> 8.7, h2 12.1 -> 9.9, h3
+// 9.8 -> 8.8, h4 13.0 -> 8.9 us, a mixed-precision solve 31.9 -> 27.9 ms.
+// LDS bytes per site; the padding spreads a wavefront's accesses over the banks
+template <int Ls> constexpr int lane_site_stride() { return 24 * Ls * 2 + Ls * 2; }
+
+template <typename Geo, typename S, int Ls, bool DAG, bool HASW>
+__global__ void __launch_bounds__(16 * Ls) __attribute__((amdgpu_waves_per_eu(2)))
+k_hop_lane(Geo geo, Field<S> out_b, Field<S> in_b, Field<S> w_b, Field<S> dotf_b, const float* E0, const float* E1,
+           double* dot_partial, HopWork wk) {
+  constexpr uint32_t CB = sizeof(typename Field<S>::chunk);
+  constexpr int NS = 64 / Ls, NG = NS / 4, NW = Ls / 4, STR = lane_site_stride<Ls>();
+  constexpr bool DOT = DAG && HASW;
+  __shared__ __align__(16) unsigned char tiles[NW * NS * STR];
+  __shared__ double red[NW];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int col = lane & 15, g2 = lane >> 4;
+  const int j = g2 + 4 * (col / Ls), s = col % Ls;   // the lane's site of the wavefront, and slice
+  int64_t blk;
+  int rhs;
+  wk.decode(blockIdx.x, gridDim.x, blk, rhs);
+  if (wk.mask && wk.mask[rhs] == 0) return;   // uniform over the workgroup
+  blk = geo.physical(blk);
+  const Field<S> out = out_b.at(rhs), in = in_b.at(rhs);
+  const SiteRef ref = geo.locate(blk, wave * NS + j, 16, Ls, s);
+  const WaveSite<Geo> ws(geo, ref);
+  const uint32_t mask = ws.mask();
+  const uint32_t oo = ref.valid ? (uint32_t)ref.out5 * CB : kAbsent;
+  const uint32_t wo = HASW && ref.valid && ref.w5 >= 0 ? (uint32_t)ref.w5 * CB : kAbsent;
+  const bool live = HASW && __builtin_amdgcn_ballot_w64(wo != kAbsent) != 0;
+
+  const ChunkRsrc<S> rs(in);
+  const __amdgpu_buffer_rsrc_t lr = make_rsrc(geo.g.data, (uint64_t)80 * (uint64_t)geo.g.vh * 4u);
+  Raw<S> q[8], wq, pq;
+  u32x4 lw[8];
+  auto load_term = [&](auto kc) {
+    constexpr int K = decltype(kc)::value;
+    const uint32_t a = (uint32_t)min(lane & 3, 2), par = K % 2 == 0 ? geo.par : 1 - geo.par;
+    const uint32_t lo = ((((par * 4 + K / 2) * (uint32_t)geo.g.vh + ws.template link_site<K>(geo)) * 40u) |
+                         ws.template absent<K>()) + 4u * (K % 2 == 0 ? 3 * a : a);
+    constexpr uint32_t step = K % 2 == 0 ? 4 : 12;
+    lw[K].x = __builtin_amdgcn_raw_buffer_load_b32(lr, lo, 0, 0);
+    lw[K].y = __builtin_amdgcn_raw_buffer_load_b32(lr, lo + step, 0, 0);
+    lw[K].z = __builtin_amdgcn_raw_buffer_load_b32(lr, lo + 2 * step, 0, 0);
+    q[K].load(rs, ((ws.template in_site<K>(geo) * (uint32_t)Ls + (uint32_t)s) * CB) | ws.template absent<K>());
+  };
+  // MFMA B operands: column s of the matrices, the 4 rows of this lane's k group
+  const int kg = g2 % NW;
+  float4_t m1[2], m0[2];
+  auto load_rest = [&]() {
+    if constexpr (HASW) wq.load(ChunkRsrc<S>(w_b.at(rhs)), wo);
+    if constexpr (DOT) {
+      if (dot_partial) pq.load(ChunkRsrc<S>(dotf_b.at(rhs)), oo);
+    }
+#pragma unroll
+    for (int chi = 0; chi < 2; ++chi) {
+      m1[chi] = *reinterpret_cast<const float4_t*>(E1 + (chi * Ls + s) * Ls + 4 * kg);
+      if constexpr (HASW) m0[chi] = *reinterpret_cast<const float4_t*>(E0 + (chi * Ls + s) * Ls + 4 * kg);
+    }
+    sched_fence();
+  };
+  float acc[24];
+#pragma unroll
+  for (int k = 0; k < 24; ++k) acc[k] = 0.f;
+  auto term = [&](auto kc) {
+    constexpr int K = decltype(kc)::value;
+    constexpr bool FWD = K % 2 == 0;
+    constexpr int SIGN = (FWD ? -1 : 1) * (DAG ? -1 : 1);
+    term_mfma<K / 2, SIGN, !FWD>(q[K].halves(0), q[K].halves(1), q[K].halves(2), lw[K], q[K].s, acc);
+  };
+  if (mask == 0xffu) {   // no branch between the loads: each term waits for its own
+    static_for<8>([&](auto kc) {
+      load_term(kc);
+      sched_fence();
+    });
+    load_rest();
+    static_for<8>([&](auto kc) {
+      term(kc);
+      pin24(acc);
+    });
+  } else {
+    static_for<8>([&](auto kc) {
+      if (mask >> decltype(kc)::value & 1) load_term(kc);
+      sched_fence();
+    });
+    load_rest();
+    static_for<8>([&](auto kc) {
+      if (mask >> decltype(kc)::value & 1) term(kc);
+      pin24(acc);
+    });
+  }
+
+  // FP16 operands: every site scaled by its largest entry; the rows of the
+  // centre field are first rounded over their own largest entry
+  float rowmax = 0.f;
+  uint32_t wp[12];
+  if constexpr (HASW) {
+    float v[24];
+    wq.values(v);
+#pragma unroll
+    for (int k = 0; k < 24; ++k) rowmax = fmaxf(rowmax, fabsf(v[k]));
+    const float im = rowmax > 0.f ? 1.f / rowmax : 0.f;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) wp[k] = h2_bits(v[2 * k] * im, v[2 * k + 1] * im);
+  }
+  float cs = rowmax;
+#pragma unroll
+  for (int k = 0; k < 24; ++k) cs = fmaxf(cs, fabsf(acc[k]));
+#pragma unroll
+  for (int off = 1; off < Ls; off <<= 1) cs = fmaxf(cs, __shfl_xor(cs, off));
+  const float ics = cs > 0.f ? 1.f / cs : 0.f;
+
+  // tile: [site][component][slice]
+  unsigned char* tile = tiles + wave * (NS * STR);
+  uint16_t* mine = reinterpret_cast<uint16_t*>(tile + j * STR) + s;
+  const unsigned char* rows = tile + ((col >> 2) + 4 * (g2 / NW)) * STR + (col & 3) * (2 * Ls) + 8 * kg;
+  float4_t d[NG][6];   // a group's sums are valid in its own columns
+#pragma unroll
+  for (int i = 0; i < NG; ++i)
+#pragma unroll
+    for (int k = 0; k < 6; ++k) d[i][k] = float4_t{0.f, 0.f, 0.f, 0.f};
+  auto product = [&](const uint32_t* w, const float4_t* m) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+      mine[2 * k * Ls] = (uint16_t)w[k];
+      mine[(2 * k + 1) * Ls] = (uint16_t)(w[k] >> 16);
+    }
+    half4_t e[2];
+#pragma unroll
+    for (int chi = 0; chi < 2; ++chi)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) e[chi][v] = (_Float16)m[chi][v];
+    // the tile is the wavefront's own
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      const u32x2 x = *reinterpret_cast<const u32x2*>(rows + 4 * k * (2 * Ls));
+#pragma unroll
+      for (int i = 0; i < NG; ++i) {
+        const bool own = g2 / NW == i;
+        const u32x2 a = {own ? x.x : 0u, own ? x.y : 0u};
+        d[i][k] = __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(half4_t, a), e[k >= 3 ? 1 : 0], d[i][k], 0,
+                                                        0, 0);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  uint32_t h[12];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) h[k] = h2_bits(acc[2 * k] * ics, acc[2 * k + 1] * ics);
+  product(h, m1);
+  if constexpr (HASW) {
+    if (live) {
+      const float rsw = rowmax * ics;
+#pragma unroll
+      for (int k = 0; k < 12; ++k) h[k] = h2_bits(half_lo(wp[k]) * rsw, half_hi(wp[k]) * rsw);
+      product(h, m0);
+    }
+  }
+  float y[24];
+#pragma unroll
+  for (int k = 0; k < 24; ++k) {
+    float v = d[0][k >> 2][k & 3];
+#pragma unroll
+    for (int i = 1; i < NG; ++i) v = col / Ls == i ? d[i][k >> 2][k & 3] : v;
+    y[k] = v * cs;
+  }
+  Packed<S> pk;
+  pk.from(y);
+  const ChunkRsrc<S> ro(out);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    if constexpr (std::is_same<S, __half>::value) __builtin_amdgcn_raw_buffer_store_b128(pk.q[k], ro.c[k], oo, 0, 0);
+    else __builtin_amdgcn_raw_buffer_store_b64(pk.q[k], ro.c[k], oo, 0, 0);
+  }
+  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(pk.s), ro.sc, ref.valid ? (uint32_t)ref.out5 * 4u : kAbsent, 0, 0);
+  if constexpr (DOT) {
+    if (dot_partial) {
+      float pv[24], loc = 0.f;
+      pq.values(pv);
+#pragma unroll
+      for (int k = 0; k < 24; ++k) loc += pv[k] * y[k];
+      // the general kernel's order: a butterfly over the lanes (site, slice),
+      // slice fastest, of each wavefront, then the wavefronts in turn; site
+      // bits 0 and 1 are lane bits 4 and 5 here, further ones follow the slice
+      double v = ref.valid ? (double)loc : 0.0;
+      for (int off = 8; off >= Ls; off >>= 1) v += __shfl_xor(v, off);
+      v += __shfl_xor(v, 32);
+      v += __shfl_xor(v, 16);
+      for (int off = Ls / 2; off > 0; off >>= 1) v += __shfl_xor(v, off);
+      if (lane == 0) red[wave] = v;
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        double tot = 0;
+        for (int i = 0; i < NW; ++i) tot += red[i];
+        dot_partial[(int64_t)rhs * wk.nblk + blk] = tot;
       }
     }
   }
