@@ -454,7 +454,7 @@ def kernels_bench(args):
     print(json.dumps(out), flush=True)
 
 
-KERNEL_SOURCES = ["common.h", "sitekern.h", "kernels.h", "kernels.hip", "sub.hip"]
+KERNEL_SOURCES = ["common.h", "sitekern.h", "wavekern.h", "kernels.h", "kernels.hip", "sub.hip"]
 def traffic_summary(workload):
     return os.path.join(ROOT, "profiles", f"hop_kernels_{workload}_hbm_traffic.md")
 PROF_STRIDE = 8   # hop launches per timed launch in the bench's timed region
