@@ -1,6 +1,9 @@
-"""Subdomain hops with Ls a multiple of 4: the kernel that gives a wavefront 16
-output sites, at every Ls it takes, on tilings whose regions end inside a
-block of 16 sites and whose rim sites have one to eight of the eight terms.
+"""Subdomain hops with Ls a multiple of 4 in small launches, on tilings whose
+regions end inside a block of 16 sites and whose rim sites have one to eight of
+the eight terms: the kernel that gives a wavefront 16 output sites (FP32, and
+FP16 with Ls 12), the one with a lane per 5D site (the 16- and 8-bit formats with
+Ls 4, 8 and 16) and the general one.  Launches past the sizes of the second are
+in test_gpu_hop_limits.
 
 FP32 against the exact local operator within 1e-6, the bound of an FP32
 operator application; FP16 and INT8 against 2.5 times the error the format
