@@ -156,8 +156,11 @@ __device__ __forceinline__ double fused_beta(const double* rr, int bps, int64_t 
 // number times its scale, and that product is the one that joins the addition
 // in the fused multiply-add; for FP16 component SWAP has them the other way
 // round.  All of it is written out because 16-bit storage turns one rounding
-// into another stored value: the preconditioner's output is what it was to the
-// bit when these updates were kernels of their own, contracted by the compiler.
+// into another stored value, and the updates that were kernels of their own
+// had this rounding (SWAP is what their compilation chose).  Either order is as
+// exact: without SWAP the preconditioner (16^3x32 x 12, FP16, k = 6) is 6.4e-4
+// from its value in 64 bits, as with it, but 3.0e-4 from what it returned
+// before, so the rounding stays; tests/test_gpu_inner_rounding.py holds it.
 template <int SWAP, typename S, typename T>
 __device__ __forceinline__ void load_site_add(const Field<S>& f, uint32_t i, T coef, const T* x, T* v) {
   T t[24];
