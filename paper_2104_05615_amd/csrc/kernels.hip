@@ -89,20 +89,47 @@ static HopWork hop_work(int64_t nblk, const Batch& bt, const Sched& sc) {
 // of 4 (up to 16) in FP32, FP16 and INT8 storage, where the MFMA epilogue is
 // on: the non-adjoint hops h1 and h2, whose output regions grow past their
 // input so that many sites lack some of the eight terms, and the 8-bit
-// format's adjoint ones.  Measured per launch, general kernel -> this one:
-//   16^3x32 x 12, FP16, 4^3x8: h1 81 -> 74, h2 211 -> 160 us (h3 122 -> 132,
-//     h4 69 -> 69); 32^3x64 x 12, FP16, 8^3x16: h1 951 -> 847, h2 1867 -> 1542
-//     (h3 1157 -> 1222, h4 848 -> 899)
-//   16^4 x 8, FP32, 4^4: h1 57 -> 57, h2 163 -> 114 (h3 89 -> 104, h4 50 -> 54)
-//   16^4 x 16, INT8, 4^4: h1 59 -> 47, h2 160 -> 96, h3 67 -> 63, h4 44 -> 34
-// In h3 and h4 every site has all eight terms and the general kernel's three
-// or four wavefronts per 16 sites keep more of the neighbours in L1.
+// format's adjoint ones.  In FP16 and FP32 h3 and h4 every site has all eight
+// terms and the general kernel's three or four wavefronts per 16 sites keep
+// more of the neighbours in L1.  Measured per launch, us, general kernel ->
+// this one:
+//   FP16, Ls 12: 16^3x32, 4^3x8, h1 81 -> 74, h2 211 -> 160 (h3 122 -> 132,
+//     h4 69 -> 69); 32^3x64, 8^3x16, h1 951 -> 847, h2 1867 -> 1542 (h3 1157 ->
+//     1222, h4 848 -> 899)
+//   INT8, Ls 16: 16^4, 4^4, h1 59 -> 47, h2 160 -> 96, h3 67 -> 63, h4 44 -> 34
+//   FP32 h2: 8^4, 4^4, Ls 4 17.2 -> 11.2, Ls 8 18.2 -> 15.8, Ls 12 20.7 -> 20.2,
+//     Ls 16 27.7 -> 24.4; 24^3x48, 6^3x12, 649 -> 426, 1112 -> 850, 1406 -> 1264,
+//     2109 -> 1599
+// Exceptions, where its one wavefront, with Ls / 4 slices of a site in series in
+// each lane, is the longer chain or keeps too few neighbours in L1:
+//   FP32 h1 with Ls 12 and 16: 8^4 13.5 -> 17.0 and 14.9 -> 20.2, 16^4 82 -> 85 and
+//     100 -> 105, 24^3x48 603 -> 646 and 754 -> 789
+//   FP32 h1 with Ls 8 but for launches of 1025 to 16384 blocks of 16 sites; at so
+//     many blocks: 12.8 -> 13.1 at 384, 14.2 -> 14.8 at 704, 15.0 -> 15.1 at 768,
+//     17.5 -> 17.0 at 1088, 26.9 -> 24.7 at 2560, 58.4 -> 57.7 at 6520, 105.9 ->
+//     104.7 at 11264, 190 -> 203 at 18016, 289 -> 302 at 31232, 413 -> 433 at 45056
+//     (Ls 4: 12.5 -> 10.3 at 384, 263 -> 239 at 45056)
+//   INT8 with Ls 12 in launches of up to 1024 blocks (one such wavefront per
+//     SIMD; h3, which has no centre field, 512; h2 gains at every size); at so
+//     many blocks: h1 11.5 -> 12.9 at 384, 12.7 -> 14.0 at 544, 13.0 -> 13.2 at
+//     704, 25.0 -> 22.6 at 2560; h3 11.6 -> 12.7 at 384, 13.7 -> 12.9 at 544, 14.2
+//     -> 13.7 at 704; h4 13.3 -> 15.8 at 128, 13.8 -> 16.3 at 256, 18.7 -> 18.5 at
+//     656, 21.5 -> 23.5 at 1024, 28.8 -> 25.2 at 1440
 template <typename Geo, typename S> struct WaveHops {
-  static constexpr bool plain = false, adjoint = false;
+  static constexpr bool any = false;
 };
-template <> struct WaveHops<SubGeo<float, float>, float> { static constexpr bool plain = true, adjoint = false; };
-template <> struct WaveHops<SubGeo<float, __half, true>, __half> { static constexpr bool plain = true, adjoint = false; };
-template <> struct WaveHops<SubGeo<float, __half, true>, int8_t> { static constexpr bool plain = true, adjoint = true; };
+template <> struct WaveHops<SubGeo<float, float>, float> { static constexpr bool any = true; };
+template <> struct WaveHops<SubGeo<float, __half, true>, __half> { static constexpr bool any = true; };
+template <> struct WaveHops<SubGeo<float, __half, true>, int8_t> { static constexpr bool any = true; };
+
+template <typename S> static bool wave_takes(int Ls, bool dagger, bool has_w, int64_t nblk) {
+  if (Ls % 4 != 0) return false;
+  if (std::is_same<S, float>::value)
+    return !dagger && (has_w || Ls == 4 || (Ls == 8 && nblk > 1024 && nblk <= 16384));
+  if (std::is_same<S, __half>::value) return !dagger;
+  if (Ls == 12 && (dagger || !has_w)) return nblk > (dagger && !has_w ? 512 : 1024);
+  return true;
+}
 
 // The lane-per-5D-site kernel serves the 16- and 8-bit formats' subdomain hops
 // with Ls 4, 8 or 16 before both: launches of up to 3072 wavefronts (three per
@@ -180,7 +207,7 @@ static void launch_hop_mf(hipStream_t st, const Geo& geo, int64_t nblocks, const
   const HopWork wk = hop_work(nblocks, bt, sc);
   dim3 grid((unsigned)(nblocks * bt.n)), block(site_block_threads(ns, Ls));
   const int wid = epi.w_identity ? 1 : 0;
-  if constexpr (MF && WaveHops<Geo, S>::plain && sizeof(S) < 4) {
+  if constexpr (MF && WaveHops<Geo, S>::any && sizeof(S) < 4) {
     if (E1 && (!w || tileB) && lane_hop<S>(Ls, dagger, w != nullptr, nblocks * bt.n)) {
       auto go = [&](auto lc, auto dag) {
         launch_hop_lane<Geo, S, decltype(lc)::value, decltype(dag)::value>(
@@ -197,9 +224,9 @@ static void launch_hop_mf(hipStream_t st, const Geo& geo, int64_t nblocks, const
       return;
     }
   }
-  if constexpr (MF && WaveHops<Geo, S>::plain) {
-    if (Ls % 4 == 0 && E1 && (!w || tileB) && !(dagger && !WaveHops<Geo, S>::adjoint)) {
-      if constexpr (WaveHops<Geo, S>::adjoint) {
+  if constexpr (MF && WaveHops<Geo, S>::any) {
+    if (E1 && (!w || tileB) && wave_takes<S>(Ls, dagger, w != nullptr, nblocks * bt.n)) {
+      if constexpr (std::is_same<S, int8_t>::value) {
         if (dagger) {
           launch_hop_wave<Geo, S, true>(st, geo, grid, typed<S>(out), typed<S>(in), w != nullptr, wf, df, Ls, E0, E1,
                                         epi.dot_partial, wk);

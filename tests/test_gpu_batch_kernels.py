@@ -16,8 +16,8 @@ pytestmark = pytest.mark.gpu
 DIMS, SUB, NRHS = (8, 8, 8, 8), (4, 4, 4, 4), 13
 
 
-@pytest.mark.parametrize("inner,Ls", [("fp16", 4), ("fp16", 8), ("fp16", 16), ("int8", 8),
-                                      ("int8", 16)])
+@pytest.mark.parametrize("inner,Ls", [("fp16", 4), ("fp16", 8), ("fp16", 16), ("int8", 8), ("int8", 12),
+                                      ("int8", 16), ("fp32", 8)])
 def test_batch_equals_single_solves_across_kernels(inner, Ls):
     import torch
     from paper_2104_05615_amd import MSPCG
