@@ -122,7 +122,7 @@ template <> struct WaveHops<SubGeo<float, float>, float> { static constexpr bool
 template <> struct WaveHops<SubGeo<float, __half, true>, __half> { static constexpr bool any = true; };
 template <> struct WaveHops<SubGeo<float, __half, true>, int8_t> { static constexpr bool any = true; };
 
-template <typename S> static bool wave_takes(int Ls, bool dagger, bool has_w, int64_t nblk) {
+template <typename S> constexpr bool wave_takes(int Ls, bool dagger, bool has_w, int64_t nblk) {
   if (Ls % 4 != 0) return false;
   if (std::is_same<S, float>::value)
     return !dagger && (has_w || Ls == 4 || (Ls == 8 && nblk > 1024 && nblk <= 16384));
@@ -147,47 +147,47 @@ template <typename S> static bool wave_takes(int Ls, bool dagger, bool has_w, in
 //     x 8: h3 248 -> 225 (h1 178 -> 186, h2 351 -> 371, h4 164 -> 168)
 // In the rest the link that the wavefront kernel loads once per Ls / 4 slices,
 // or the general kernel's reuse of neighbours in L1, weighs more.
-template <typename S> static bool lane_hop(int Ls, bool dagger, bool has_w, int64_t nblk) {
+template <typename S> constexpr bool lane_takes(int Ls, bool dagger, bool has_w, int64_t nblk) {
   if (Ls != 4 && Ls != 8 && Ls != 16) return false;
   if (nblk * (Ls / 4) <= 3072) return true;
   if (std::is_same<S, int8_t>::value) return Ls == 4 || (Ls == 8 && dagger && !has_w);
   return dagger && (has_w || Ls <= 8);
 }
 
-template <typename Geo, typename S, int Ls, bool DAG>
-static void launch_hop_lane(hipStream_t st, const Geo& geo, dim3 grid, Field<S> out, Field<S> in, bool has_w,
-                            Field<S> wf, Field<S> df, const float* E0, const float* E1, double* dot,
-                            const HopWork& wk) {
-  const dim3 block(16 * Ls);
-  if (has_w) hipLaunchKernelGGL((k_hop_lane<Geo, S, Ls, DAG, true>), grid, block, 0, st, geo, out, in, wf, df, E0, E1,
-                                dot, wk);
-  else hipLaunchKernelGGL((k_hop_lane<Geo, S, Ls, DAG, false>), grid, block, 0, st, geo, out, in, wf, df, E0, E1, dot,
-                          wk);
+enum class SubHop { General, Wave, Lane };
+template <typename S> constexpr SubHop sub_hop(int Ls, bool dagger, bool has_w, int64_t nblk) {
+  if (sizeof(S) < 4 && lane_takes<S>(Ls, dagger, has_w, nblk)) return SubHop::Lane;
+  return wave_takes<S>(Ls, dagger, has_w, nblk) ? SubHop::Wave : SubHop::General;
 }
 
-template <typename Geo, typename S, int LC, bool DAG>
-static void launch_hop_wave_lc(hipStream_t st, const Geo& geo, dim3 grid, Field<S> out, Field<S> in, bool has_w,
-                               Field<S> wf, Field<S> df, const float* E0, const float* E1, double* dot,
-                               const HopWork& wk) {
-  const dim3 block(64);
-  if (has_w) hipLaunchKernelGGL((k_hop_wave<Geo, S, LC, DAG, true>), grid, block, 0, st, geo, out, in, wf, df, E0, E1,
-                                dot, wk);
-  else hipLaunchKernelGGL((k_hop_wave<Geo, S, LC, DAG, false>), grid, block, 0, st, geo, out, in, wf, df, E0, E1, dot,
-                          wk);
+// the instances there are (the lane kernel: all of Ls 4, 8 and 16)
+template <typename S> constexpr bool has_wave(int Ls, bool dagger, bool has_w) {
+  return std::is_same<S, int8_t>::value ? Ls > 4 : !dagger;
 }
 
-template <typename Geo, typename S, bool DAG>
-static void launch_hop_wave(hipStream_t st, const Geo& geo, dim3 grid, Field<S> out, Field<S> in, bool has_w,
-                            Field<S> wf, Field<S> df, int Ls, const float* E0, const float* E1, double* dot,
-                            const HopWork& wk) {
-  switch (Ls / 4) {
-    case 1:
-      if constexpr (!std::is_same<S, int8_t>::value)   // INT8 with Ls 4: lane_hop
-        launch_hop_wave_lc<Geo, S, 1, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk);
-      break;
-    case 2: launch_hop_wave_lc<Geo, S, 2, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk); break;
-    case 3: launch_hop_wave_lc<Geo, S, 3, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk); break;
-    default: launch_hop_wave_lc<Geo, S, 4, DAG>(st, geo, grid, out, in, has_w, wf, df, E0, E1, dot, wk); break;
+// no launch that sub_hop can make, on either side of each of its bounds, lacks its kernel
+template <typename S> constexpr bool hops_have_kernels() {
+  constexpr int64_t n[] = {1, 192, 193, 512, 513, 768, 769, 1024, 1025, 1536, 1537, 3072, 3073, 16384, 16385, 1 << 30};
+  for (int Ls = 4; Ls <= 16; Ls += 4)
+    for (int64_t nblk : n)
+      for (int f = 0; f < 4; ++f)
+        if (sub_hop<S>(Ls, f & 1, f & 2, nblk) == SubHop::Wave && !has_wave<S>(Ls, f & 1, f & 2)) return false;
+  return true;
+}
+static_assert(hops_have_kernels<float>() && hops_have_kernels<__half>() && hops_have_kernels<int8_t>(),
+              "a subdomain hop's kernel is not instantiated");
+
+template <typename F> static void by_flag(bool v, F&& f) {
+  if (v) f(std::true_type());
+  else f(std::false_type());
+}
+template <typename F> static void by_ls(int Ls, F&& f) {
+  switch (Ls) {
+    case 4: f(std::integral_constant<int, 4>()); break;
+    case 8: f(std::integral_constant<int, 8>()); break;
+    case 12: f(std::integral_constant<int, 12>()); break;
+    case 16: f(std::integral_constant<int, 16>()); break;
+    default: throw std::runtime_error("hop: Ls is no multiple of 4 up to 16");
   }
 }
 
@@ -207,35 +207,28 @@ static void launch_hop_mf(hipStream_t st, const Geo& geo, int64_t nblocks, const
   const HopWork wk = hop_work(nblocks, bt, sc);
   dim3 grid((unsigned)(nblocks * bt.n)), block(site_block_threads(ns, Ls));
   const int wid = epi.w_identity ? 1 : 0;
-  if constexpr (MF && WaveHops<Geo, S>::any && sizeof(S) < 4) {
-    if (E1 && (!w || tileB) && lane_hop<S>(Ls, dagger, w != nullptr, nblocks * bt.n)) {
-      auto go = [&](auto lc, auto dag) {
-        launch_hop_lane<Geo, S, decltype(lc)::value, decltype(dag)::value>(
-            st, geo, grid, typed<S>(out), typed<S>(in), w != nullptr, wf, df, E0, E1, epi.dot_partial, wk);
-      };
-      auto by_ls = [&](auto dag) {
-        if (Ls == 4) go(std::integral_constant<int, 4>(), dag);
-        else if (Ls == 8) go(std::integral_constant<int, 8>(), dag);
-        else go(std::integral_constant<int, 16>(), dag);
-      };
-      if (dagger) by_ls(std::true_type());
-      else by_ls(std::false_type());
-      LAUNCH_CHECK();
-      return;
-    }
-  }
   if constexpr (MF && WaveHops<Geo, S>::any) {
-    if (E1 && (!w || tileB) && wave_takes<S>(Ls, dagger, w != nullptr, nblocks * bt.n)) {
-      if constexpr (std::is_same<S, int8_t>::value) {
-        if (dagger) {
-          launch_hop_wave<Geo, S, true>(st, geo, grid, typed<S>(out), typed<S>(in), w != nullptr, wf, df, Ls, E0, E1,
-                                        epi.dot_partial, wk);
-          LAUNCH_CHECK();
-          return;
-        }
-      }
-      launch_hop_wave<Geo, S, false>(st, geo, grid, typed<S>(out), typed<S>(in), w != nullptr, wf, df, Ls, E0, E1,
-                                     epi.dot_partial, wk);
+    const SubHop kernel = E1 && (!w || tileB) ? sub_hop<S>(Ls, dagger, w != nullptr, nblocks * bt.n) : SubHop::General;
+    if (kernel != SubHop::General) {
+      by_ls(Ls, [&](auto ls) {
+        by_flag(dagger, [&](auto dag) {
+          by_flag(w != nullptr, [&](auto hw) {
+            constexpr int L = decltype(ls)::value;
+            constexpr bool D = decltype(dag)::value, W = decltype(hw)::value;
+            if (kernel == SubHop::Lane) {
+              if constexpr (sizeof(S) < 4 && L != 12)
+                hipLaunchKernelGGL((k_hop_lane<Geo, S, L, D, W>), grid, dim3(16 * L), 0, st, geo, typed<S>(out),
+                                   typed<S>(in), wf, df, E0, E1, epi.dot_partial, wk);
+              else throw std::runtime_error("hop: no lane kernel for this storage and Ls");
+            } else {
+              if constexpr (has_wave<S>(L, D, W))
+                hipLaunchKernelGGL((k_hop_wave<Geo, S, L / 4, D, W>), grid, dim3(64), 0, st, geo, typed<S>(out),
+                                   typed<S>(in), wf, df, E0, E1, epi.dot_partial, wk);
+              else throw std::runtime_error("hop: no wavefront kernel for this storage, Ls and hop");
+            }
+          });
+        });
+      });
       LAUNCH_CHECK();
       return;
     }
