@@ -160,9 +160,16 @@ template <typename S> constexpr SubHop sub_hop(int Ls, bool dagger, bool has_w, 
   return wave_takes<S>(Ls, dagger, has_w, nblk) ? SubHop::Wave : SubHop::General;
 }
 
-// the instances there are (the lane kernel: all of Ls 4, 8 and 16)
+// the instances there are: those that sub_hop reaches (the lane kernel: all of
+// Ls 4, 8 and 16)
 template <typename S> constexpr bool has_wave(int Ls, bool dagger, bool has_w) {
-  return std::is_same<S, int8_t>::value ? Ls > 4 : !dagger;
+  if (std::is_same<S, float>::value) return !dagger && (has_w || Ls <= 8);
+  if (std::is_same<S, __half>::value) return !dagger;
+  return Ls > 8 || (Ls == 8 && (!dagger || has_w));
+}
+template <typename S> constexpr bool has_general(bool dagger, bool has_w) {
+  if (std::is_same<S, float>::value) return true;
+  return dagger || (std::is_same<S, int8_t>::value && !has_w);
 }
 
 // no launch that sub_hop can make, on either side of each of its bounds, lacks its kernel
@@ -170,8 +177,11 @@ template <typename S> constexpr bool hops_have_kernels() {
   constexpr int64_t n[] = {1, 192, 193, 512, 513, 768, 769, 1024, 1025, 1536, 1537, 3072, 3073, 16384, 16385, 1 << 30};
   for (int Ls = 4; Ls <= 16; Ls += 4)
     for (int64_t nblk : n)
-      for (int f = 0; f < 4; ++f)
-        if (sub_hop<S>(Ls, f & 1, f & 2, nblk) == SubHop::Wave && !has_wave<S>(Ls, f & 1, f & 2)) return false;
+      for (int f = 0; f < 4; ++f) {
+        const SubHop k = sub_hop<S>(Ls, f & 1, f & 2, nblk);
+        if (k == SubHop::Wave && !has_wave<S>(Ls, f & 1, f & 2)) return false;
+        if (k == SubHop::General && !has_general<S>(f & 1, f & 2)) return false;
+      }
   return true;
 }
 static_assert(hops_have_kernels<float>() && hops_have_kernels<__half>() && hops_have_kernels<int8_t>(),
@@ -233,17 +243,15 @@ static void launch_hop_mf(hipStream_t st, const Geo& geo, int64_t nblocks, const
       return;
     }
   }
-  if (dagger) {
-    if (w) hipLaunchKernelGGL((k_hop<Geo, S, true, true, MF>), grid, block, lds, st, geo, typed<S>(out), typed<S>(in), wf,
-                              df, Ls, ns, E0, E1, wid, epi.dot_partial, wk);
-    else hipLaunchKernelGGL((k_hop<Geo, S, true, false, MF>), grid, block, lds, st, geo, typed<S>(out), typed<S>(in),
-                            wf, df, Ls, ns, E0, E1, wid, epi.dot_partial, wk);
-  } else {
-    if (w) hipLaunchKernelGGL((k_hop<Geo, S, false, true, MF>), grid, block, lds, st, geo, typed<S>(out), typed<S>(in),
-                              wf, df, Ls, ns, E0, E1, wid, epi.dot_partial, wk);
-    else hipLaunchKernelGGL((k_hop<Geo, S, false, false, MF>), grid, block, lds, st, geo, typed<S>(out), typed<S>(in),
-                            wf, df, Ls, ns, E0, E1, wid, epi.dot_partial, wk);
-  }
+  by_flag(dagger, [&](auto dag) {
+    by_flag(w != nullptr, [&](auto hw) {
+      constexpr bool D = decltype(dag)::value, W = decltype(hw)::value;
+      if constexpr (!(MF && WaveHops<Geo, S>::any) || has_general<S>(D, W))
+        hipLaunchKernelGGL((k_hop<Geo, S, D, W, MF>), grid, block, lds, st, geo, typed<S>(out), typed<S>(in), wf, df, Ls,
+                           ns, E0, E1, wid, epi.dot_partial, wk);
+      else throw std::runtime_error("hop: no general kernel for this storage and hop");
+    });
+  });
   LAUNCH_CHECK();
 }
 

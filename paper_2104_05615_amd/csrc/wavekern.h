@@ -351,15 +351,15 @@ __device__ __forceinline__ void tile_b16(const unsigned char* row0, int q0, half
 }
 
 // y = E0 w (centre field, where it exists) + E1 h, h the hop, and optionally
-// <dotf, y> per 16 sites; E1 is never null, E0 with HASW neither.
+// <dotf, y> per 16 sites (8-bit format only: FP32 and FP16 have no adjoint hop
+// here); E1 is never null, E0 with HASW neither.
 //
 // What bounds it: a region hop's reads through the L1 (every spinor is read
-// by up to eight sites; 8-9 TB/s of L1 misses in the adjoint hops) and, at the
-// rim sites with one or two of the eight terms, the epilogue.  The term loop
-// skips what no site of the wavefront has by a scalar branch (the regions are
-// ordered by neighbour pattern), and nothing but the wavefront itself waits in
-// the epilogue: h2 (N2 <- N1, 12 FP16 slices, 256 subdomains of 8^3x16) 1867 ->
-// 1542 us, at 256 of 4^3x8 211 -> 160 us.
+// by up to eight sites) and, at the rim sites with one or two of the eight
+// terms, the epilogue.  The term loop skips what no site of the wavefront has by
+// a scalar branch (the regions are ordered by neighbour pattern), and nothing
+// but the wavefront itself waits in the epilogue: h2 (N2 <- N1, 12 FP16 slices,
+// 256 subdomains of 8^3x16) 1867 -> 1542 us, at 256 of 4^3x8 211 -> 160 us.
 template <typename Geo, typename S, int LC, bool DAG, bool HASW>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 k_hop_wave(Geo geo, Field<S> out_b, Field<S> in_b, Field<S> w_b, Field<S> dotf_b, const float* E0, const float* E1,
@@ -389,10 +389,8 @@ k_hop_wave(Geo geo, Field<S> out_b, Field<S> in_b, Field<S> w_b, Field<S> dotf_b
 
   if constexpr (std::is_same<S, float>::value) {
     // FP32: one chirality (12 components, 48-byte rows) at a time
+    static_assert(!DAG, "FP32: no fused dot");
     const int ic = min(col, Ls - 1);
-    float loc[LC];
-#pragma unroll
-    for (int r = 0; r < LC; ++r) loc[r] = 0.f;
 #pragma unroll
     for (int chi = 0; chi < 2; ++chi) {
       u32x4 wq[LC][3];
@@ -459,25 +457,8 @@ k_hop_wave(Geo geo, Field<S> out_b, Field<S> in_b, Field<S> w_b, Field<S> dotf_b
         for (int k = 0; k < 3; ++k) {
           const u32x4 c = *reinterpret_cast<const u32x4*>(mine + r * 192 + k * 16);
           __builtin_amdgcn_raw_buffer_store_b128(c, ro.c[3 * chi + k], oo + r * 4 * CB, 0, 0);
-          if constexpr (DOT) {
-            if (dot_partial) {
-              const ChunkRsrc<S> rp(dotf_b.at(rhs));
-              const u32x4 p = __builtin_amdgcn_raw_buffer_load_b128(rp.c[3 * chi + k], oo + r * 4 * CB, 0, 0);
-#pragma unroll
-              for (int i = 0; i < 4; ++i) loc[r] += __uint_as_float(p[i]) * __uint_as_float(c[i]);
-            }
-          }
         }
       __syncthreads();
-    }
-    if constexpr (DOT) {
-      if (dot_partial) {
-        float* buf = reinterpret_cast<float*>(tile);
-#pragma unroll
-        for (int r = 0; r < LC; ++r) buf[j * Ls + 4 * r + g] = loc[r];
-        const double tot = wave_dot<LC>(buf, lane);
-        if (lane == 0) dot_partial[(int64_t)rhs * wk.nblk + blk] = tot;
-      }
     }
   } else {
     // FP16 operands: every site column scaled by its largest entry; the rows
@@ -643,10 +624,11 @@ k_hop_wave(Geo geo, Field<S> out_b, Field<S> in_b, Field<S> w_b, Field<S> dotf_b
 // and the epilogue's MFMAs have 4 sites x 4 components as rows and slices as
 // columns, one group of 4 sites after the other (each in its part of the k
 // range), so a lane ends with the 24 components of the 5D site that it began
-// with and stores them from its registers.  At 8^4 x 8, FP16, 16 subdomains of
-// 4^4, h4 as the wavefront kernel spent 2000 of 21000 cycles on its tables,
-// 7000 on the hop, 2000 waiting for the centre field, 3100 on the products and
-// 7000 on packing and the dot; per launch h1 9.6 -> 8.7, h2 12.1 -> 9.9, h3
+// with and stores them from its registers.  Tried before it at 8^4 x 8, FP16, 16
+// subdomains of 4^4: an instance of the wavefront kernel for h4, which spent
+// 2000 of its 21000 cycles on the tables, 7000 on the hop, 2000 waiting for the
+// centre field, 3100 on the products and 7000 on packing and the dot.  Per
+// launch from the faster of the other two kernels h1 9.6 -> 8.7, h2 12.1 -> 9.9, h3
 // 9.8 -> 8.8, h4 13.0 -> 8.9 us, a mixed-precision solve 31.9 -> 27.9 ms.
 // LDS bytes per site; the padding spreads a wavefront's accesses over the banks
 template <int Ls> constexpr int lane_site_stride() { return 24 * Ls * 2 + Ls * 2; }
