@@ -135,10 +135,11 @@ template <typename S> constexpr bool wave_takes(int Ls, bool dagger, bool has_w,
 // with Ls 4, 8 or 16 before both: launches of up to 3072 wavefronts (three per
 // SIMD), where the time is one wavefront's chain, and at every size those hops
 // that its epilogue without redistribution makes faster.  Measured per launch,
-// us, the other kernels -> this one:
-//   wavefronts, FP16, Ls 8: 512 (h4) 13.0 -> 8.9; 768 (h1) 9.6 -> 8.7; 1664 (h2)
-//     12.1 -> 9.9; 3328 (h2) 15.6 -> 15.6; 3840 (h2) 19.2 -> 21.3; Ls 16: 1536
-//     (h1) 12.6 -> 9.6; 2624 (h3) 23.7 -> 22.6; 4480 (h1) 18.9 -> 21.9
+// us, the other kernels -> this one, with the launch's wavefronts:
+//   FP16, 4^4 and 6^4 subdomains: Ls 8 h4 256 13.0 -> 8.9, h1 768 9.6 -> 8.7, h2
+//     1664 12.1 -> 9.9, 3328 15.6 -> 15.6, 5632 19.2 -> 21.3; Ls 16 h1 1536 12.6 ->
+//     9.6, h4 2624 20.9 -> 17.9, h2 3328 16.2 -> 15.7, h1 6080 18.9 -> 21.9, h3
+//     6080 23.7 -> 22.6
 //   FP16 h4: 16^4 x 16, 4^4 52.8 -> 40.4; 24^3x48 x 4, 6^3x12 137 -> 117;
 //     32^3x64 x 8, 8^3x16 623 -> 579, x 16 1196 -> 1129
 //   FP16 h3: 24^3x48 x 4 199 -> 192, x 8 314 -> 295; 32^3x64 x 8 825 -> 806
@@ -146,7 +147,11 @@ template <typename S> constexpr bool wave_takes(int Ls, bool dagger, bool has_w,
 //   INT8, 24^3x48 x 4: h1 127 -> 111, h2 242 -> 211, h3 169 -> 146, h4 126 -> 100;
 //     x 8: h3 248 -> 225 (h1 178 -> 186, h2 351 -> 371, h4 164 -> 168)
 // In the rest the link that the wavefront kernel loads once per Ls / 4 slices,
-// or the general kernel's reuse of neighbours in L1, weighs more.
+// or the general kernel's reuse of neighbours in L1, weighs more.  Where that
+// begins differs between types and Ls, and one bound for all of them refuses
+// some launches that this kernel does faster: INT8 Ls 16 h1 6080 21.7 -> 18.3,
+// h2 11264 34.3 -> 31.0, h3 6080 24.7 -> 21.4; INT8 Ls 8 h1 12288 33.3 -> 30.4, h4
+// 4096 28.5 -> 24.6; FP16 Ls 4 h1 6144 22.3 -> 20.1, h2 13312 43.2 -> 39.4.
 template <typename S> constexpr bool lane_takes(int Ls, bool dagger, bool has_w, int64_t nblk) {
   if (Ls != 4 && Ls != 8 && Ls != 16) return false;
   if (nblk * (Ls / 4) <= 3072) return true;
