@@ -84,13 +84,16 @@ def stage_bytes(cfg, inner_prec):
     return out, (nC, nN1, nN2)
 
 
+# the hop stages, by the kernels of the workloads with Ls 12 and an FP16
+# preconditioner (other types and Ls run h1 to h4 on k_hop, k_hop_wave or
+# k_hop_lane, by the library's rule)
 STAGE_NAMES = {
     21: "k_hop<FullGeo,float,dag=0,w=0>: a = Q D^w_oe t0 (outer A, hop 1)",
     22: "k_hop<FullGeo,float,dag=0,w=1>: c = M5^-dag(p - M5^-1 D^w_eo a) (outer A, hop 2)",
     23: "k_hop<FullGeo,float,dag=1,w=0>: e = Q^dag D^w^dag_oe c (outer A, hop 3)",
     24: "k_hop<FullGeo,float,dag=1,w=1>: q = M5^dag c - M_phi^dag D^w^dag_eo e, <p,q> (outer A, hop 4)",
-    11: "k_hop<SubGeo,half,dag=0,w=0>: h1 N1 <- C (inner A_s)",
-    12: "k_hop<SubGeo,half,dag=0,w=1>: h2 N2 <- N1 (inner A_s)",
+    11: "k_hop_wave<SubGeo,half,dag=0,w=0>: h1 N1 <- C (inner A_s)",
+    12: "k_hop_wave<SubGeo,half,dag=0,w=1>: h2 N2 <- N1 (inner A_s)",
     13: "k_hop<SubGeo,half,dag=1,w=0>: h3 N1 <- N2 (inner A_s)",
     14: "k_hop<SubGeo,half,dag=1,w=1>: h4 C <- N1, <p_s,q_s> (inner A_s)",
 }
